@@ -11,6 +11,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -29,26 +30,20 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, b);
 }
 
-// Max / sum over lanes {l, l^16, l^32, l^48}: the four 16-lane rows of a
-// wave that hold the same MFMA column.  permlane{16,32}_swap exchange rows
-// on the VALU without going through LDS.
+// Max / sum over lanes {l, l^32}: the two lanes of a wave that hold the same
+// column of a 32x32 MFMA result.  permlane32_swap exchanges the halves on
+// the VALU without going through LDS.
 // (NaN-propagating maximum: one v_maximum_f32, no operand canonicalisation.)
-__device__ __forceinline__ float max_over_lane_rows(float v) {
-  uint32_t u = __float_as_uint(v);
+__device__ __forceinline__ float max_over_halves(float v) {
+  const uint32_t u = __float_as_uint(v);
   auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  float m = __builtin_elementwise_maximum(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  u = __float_as_uint(m);
-  auto b = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return __builtin_elementwise_maximum(__uint_as_float(b[0]), __uint_as_float(b[1]));
+  return __builtin_elementwise_maximum(__uint_as_float(a[0]), __uint_as_float(a[1]));
 }
 
-__device__ __forceinline__ float sum_over_lane_rows(float v) {
-  uint32_t u = __float_as_uint(v);
+__device__ __forceinline__ float sum_over_halves(float v) {
+  const uint32_t u = __float_as_uint(v);
   auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  float s = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  u = __float_as_uint(s);
-  auto b = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  return __uint_as_float(a[0]) + __uint_as_float(a[1]);
 }
 
 // Sum over all 64 lanes (every lane gets the total).

@@ -17,10 +17,17 @@
 //    tile (no K/V byte is read twice) the loads carry the non-temporal hint;
 //  * LDS rows are XOR-swizzled in 16-byte chunks so that both the K
 //    fragment reads (16 keys x 16 B per quarter-wave) and the transposed V
-//    reads (ds_read_b64_tr_b16) hit distinct banks;
-//  * S^T = K Q^T and O^T = V^T P^T run on v_mfma_f32_16x16x32_bf16.  In this
-//    orientation a lane owns one query row, so the online softmax needs no
-//    cross-lane traffic except a max over the four 16-lane rows;
+//    reads (ds_read_b64_tr_b16, 4 keys x 64 B per half-wave) hit distinct
+//    banks;
+//  * S^T = K Q^T and O^T = V^T P^T run on v_mfma_f32_32x32x16_bf16.  In this
+//    orientation a lane holds half the keys of one query row, so the online
+//    softmax needs no cross-lane traffic except one exchange of the two
+//    halves' maxima.  16x16x32 instructions at the same rate needed twice as
+//    many, two rows per lane and two exchanges for each (one request of 7
+//    nodes over 1500 keys 18.4 -> 17.5 us, 24 requests at D = 64 28.3 ->
+//    25.6, a rank of the 70B shape 135.8 -> 131.1, larger batches 0-2%);
+//  * a row's denominator is summed from the bf16-rounded P (the numerator's
+//    own weights) with v_dot2_f32_bf16: two P per instruction;
 //  * the softmax folds the scale into one FMA per score (exp2 of
 //    s*c - m*c) and only rescales a row's running state when its block max
 //    rises more than 2^8 above the reference;
@@ -173,17 +180,19 @@ __device__ __forceinline__ uint32_t set_bit_in(uint32_t w, int word, int v) {
 }
 
 // 16-byte chunk permutation of LDS row `row`: chunk c of the row is stored in
-// slot c ^ swizzle(row).
+// slot c ^ swizzle(row).  Any 16 consecutive rows keep one chunk in 16
+// distinct places (K reads); rows 4k .. 4k+3 keep four neighbouring chunks in
+// 16 distinct places (V reads).
 template <int NCH>
 __device__ __forceinline__ int swizzle(int row) {
-  if (NCH == 16) return ((row & 7) << 1) | ((row >> 3) & 1);
-  return (row >> 1) & 7;
+  if (NCH == 16) return ((row & 3) << 2) | ((row >> 2) & 3);
+  return ((row & 2) << 1) | ((row >> 2) & 3);
 }
 
 template <int D, bool NT>
 __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(TreeAttnArgs a) {
-  constexpr int KS = D / 32;                 // MFMA k-steps over the head dim
-  constexpr int DT = D / 16;                 // 16-wide output tiles over the head dim
+  constexpr int KS = D / 16;                 // MFMA k-steps over the head dim
+  constexpr int DT = D / 32;                 // 32-wide output tiles over the head dim
   constexpr int KB = kKeysPerBlock;          // 32 keys per pipeline stage
   constexpr int ROWB = D * 2;                // bytes per key row
   constexpr int NCH = D / 8;                 // 16-byte chunks per key row
@@ -295,24 +304,23 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(TreeAttnArg
   if (last_chunk)
     for (int i = tid; i < n; i += kThreads) par[i] = a.parent[node_base + i];
 
-  // Query fragments (B operand of S^T = K Q^T): lane holds row (lane & 15)
-  // of each 16-row block, head-dim elements ks*32 + (lane >> 4)*8 .. +7.
+  // Query fragments (B operand of S^T = K Q^T): lane holds row (lane & 31) of
+  // the wave's 32, head-dim elements ks*16 + (lane >> 5)*8 .. +7.
   const int wrow0 = row0 + wave * 32;
   const bool wave_live = wrow0 < row_end;
-  bf16x8 qf[2][KS];
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-    const int row = wrow0 + rb * 16 + (lane & 15);
-    const bool valid = row < row_end;
-    const int node = valid ? row / G : 0;
-    const int hh = valid ? row - node * G : 0;
-    const __bf16 *qp = (const __bf16 *)a.q +
-                       ((int64_t)(node_base + node) * a.num_q_heads + g * G + hh) * D + (lane >> 4) * 8;
+  const int row = wrow0 + (lane & 31);
+  const bool row_valid = row < row_end;
+  const int row_node = row_valid ? row / G : 0;
+  const int row_head = g * G + (row_valid ? row - row_node * G : 0);
+  bf16x8 qf[KS];
+  {
+    const __bf16 *qp =
+        (const __bf16 *)a.q + ((int64_t)(node_base + row_node) * a.num_q_heads + row_head) * D + (lane >> 5) * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       bf16x8 v = {};
-      if (valid) v = *(const bf16x8 *)(qp + ks * 32);
-      qf[rb][ks] = v;
+      if (row_valid) v = *(const bf16x8 *)(qp + ks * 16);
+      qf[ks] = v;
     }
   }
   // Let the start-up loads land before the first DMA, so the waits counted
@@ -434,152 +442,124 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(TreeAttnArg
   }
 
   // Per-lane LDS offsets of the MFMA operand fragments inside a stage.
-  const int q = lane >> 4, j16 = lane & 15;
+  const int half = lane >> 5;
 
-  // The ancestor sets of this lane's two rows' nodes, in registers (named
-  // scalars: an indexed array would be placed in scratch memory).
-  uint32_t an00 = 0, an01 = 0, an02 = 0, an03 = 0, an10 = 0, an11 = 0, an12 = 0, an13 = 0;
+  // The ancestor set of this lane's row's node, in registers.
+  uint32_t an0 = 0, an1 = 0, an2 = 0, an3 = 0;
   if (last_chunk) {
     __syncthreads();  // anc[] complete
-    const int node0 = min((wrow0 + j16) / G, n - 1), node1 = min((wrow0 + 16 + j16) / G, n - 1);
-    an00 = anc[node0 * 4 + 0], an01 = anc[node0 * 4 + 1], an02 = anc[node0 * 4 + 2], an03 = anc[node0 * 4 + 3];
-    an10 = anc[node1 * 4 + 0], an11 = anc[node1 * 4 + 1], an12 = anc[node1 * 4 + 2], an13 = anc[node1 * 4 + 3];
+    an0 = anc[row_node * 4 + 0], an1 = anc[row_node * 4 + 1], an2 = anc[row_node * 4 + 2], an3 = anc[row_node * 4 + 3];
   }
-  int koff[KS];  // K fragment for keys kt*16 + j16 (add kt*16*ROWB), chunk ks*4 + q
+  int koff[KS];  // K fragment: key row lane & 31, chunk ks*2 + half
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) koff[ks] = j16 * ROWB + (((ks * 4 + q) ^ swizzle<NCH>(j16)) * 16);
-  int voff[DT];  // transposed V read: key row q*4 + (j16 >> 2) (+16 for the upper half)
+  for (int ks = 0; ks < KS; ++ks)
+    koff[ks] = (lane & 31) * ROWB + (((ks * 2 + half) ^ swizzle<NCH>(lane & 31)) * 16);
+  // Transposed V reads: a 16-lane group takes 4 key rows x 16 columns; lane
+  // (half, c) of a fragment holds column dt*32 + c of key rows half*4 + 0..3
+  // (+ 8 for its upper four elements, + 16 for the second k-step).
+  int voff[DT], voff8[DT];
   {
-    const int vrow = q * 4 + (j16 >> 2);
-    const int sw = swizzle<NCH>(vrow);
+    const int j16 = lane & 15;
+    const int vrow = half * 4 + (j16 >> 2);
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-      voff[dt] = vrow * ROWB + (((dt * 2 + ((j16 & 3) >> 1)) ^ sw) * 16) + (j16 & 1) * 8;
+    for (int dt = 0; dt < DT; ++dt) {
+      const int ch = dt * 4 + ((lane >> 4) & 1) * 2 + ((j16 & 3) >> 1);
+      voff[dt] = vrow * ROWB + ((ch ^ swizzle<NCH>(vrow)) * 16) + (j16 & 1) * 8;
+      voff8[dt] = (vrow + 8) * ROWB + ((ch ^ swizzle<NCH>(vrow + 8)) * 16) + (j16 & 1) * 8;
+    }
   }
 
-  f32x4 o[2][DT];
-  f32x4 osum[2];  // row sums of P, from an all-ones V tile on the matrix cores
+  f32x16 o[DT];
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-    osum[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) o[rb][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  bf16x8 ones;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+  for (int dt = 0; dt < DT; ++dt) o[dt] = f32x16{};
+  float lsum = 0.f;                                  // sum of this lane's (rounded) P
   const float c = a.scale_log2;                      // raw score -> log2 units
   const float up_raw = kRescaleLog2 / c;             // rescale threshold in raw units
-  float m_ref[2] = {-1e30f, -1e30f};                 // reference max of this lane's row (raw units)
+  float m_ref = -1e30f;                              // reference max of this lane's row (raw units)
 
-  // S^T tiles of one block: s[rb][kt] holds keys kt*16 + q*4 + e of row j16.
-  auto scores = [&](const char *kst, f32x4 (&s)[2][2]) {
+  // S^T tile of one block: s[i] holds key (i >> 2)*8 + half*4 + (i & 3) of
+  // the lane's row.
+  auto scores = [&](const char *kst, f32x16 &s) {
+    s = f32x16{};
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      s[0][kt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      s[1][kt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 kf = *(const bf16x8 *)(kst + koff[ks] + kt * 16 * ROWB);
-        s[0][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[0][ks], s[0][kt], 0, 0, 0);
-        s[1][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[1][ks], s[1][kt], 0, 0, 0);
-      }
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8 kf = *(const bf16x8 *)(kst + koff[ks]);
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s, 0, 0, 0);
     }
   };
   // Masks the partial prefix block and the tree blocks (ancestor sets).
-  auto mask = [&](f32x4 (&s)[2][2], int blk) {
-    {
-      const bool tree_blk = blk >= n_prefix_blocks;
-      const int tb = blk - n_prefix_blocks;
-      const int valid = tree_blk ? min(KB, n - tb * KB) : min(KB, k1 - k0 - blk * KB);
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb) {
-        uint32_t aw = 0xffffffffu;
-        if (tree_blk) {
-          const uint32_t w0 = rb ? an10 : an00, w1 = rb ? an11 : an01;
-          const uint32_t w2 = rb ? an12 : an02, w3 = rb ? an13 : an03;
-          aw = (tb & 2) ? ((tb & 1) ? w3 : w2) : ((tb & 1) ? w1 : w0);
-        }
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int key = kt * 16 + q * 4 + e;
-            const bool ok = key < valid && ((aw >> key) & 1u);
-            s[rb][kt][e] = ok ? s[rb][kt][e] : -INFINITY;
-          }
-      }
+  auto mask = [&](f32x16 &s, int blk) {
+    const bool tree_blk = blk >= n_prefix_blocks;
+    const int tb = blk - n_prefix_blocks;
+    const int valid = tree_blk ? min(KB, n - tb * KB) : min(KB, k1 - k0 - blk * KB);
+    uint32_t aw = 0xffffffffu;
+    if (tree_blk) {
+      const uint32_t w0 = an0, w1 = an1, w2 = an2, w3 = an3;
+      aw = (tb & 2) ? ((tb & 1) ? w3 : w2) : ((tb & 1) ? w1 : w0);
     }
+    if (valid < KB) aw &= (1u << valid) - 1u;
+    aw >>= half * 4;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = ((aw >> ((i >> 2) * 8 + (i & 3))) & 1u) ? s[i] : -INFINITY;
   };
-  // Each row's block max.
-  auto rowmax = [&](const f32x4 (&s)[2][2], float (&bm)[2]) {
+  // The row's block max.
+  auto rowmax = [&](const f32x16 &s) {
+    float m0 = s[0], m1 = s[1];
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-      float m = __builtin_elementwise_maximum(
-          __builtin_elementwise_maximum(s[rb][0][0], s[rb][0][1]), s[rb][0][2]);
-      m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, s[rb][0][3]), s[rb][1][0]);
-      m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, s[rb][1][1]),
-                                        __builtin_elementwise_maximum(s[rb][1][2], s[rb][1][3]));
-      bm[rb] = max_over_lane_rows(m);
+    for (int i = 2; i < 14; i += 4) {
+      m0 = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m0, s[i]), s[i + 2]);
+      m1 = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m1, s[i + 1]), s[i + 3]);
     }
+    m0 = __builtin_elementwise_maximum(m0, s[14]);
+    return max_over_halves(__builtin_elementwise_maximum(__builtin_elementwise_maximum(m0, m1), s[15]));
   };
   // Raises the reference max of the rows whose block max went more than
   // 2^8 above it, rescaling their running numerator and denominator.
-  auto rescale = [&](const float (&bm)[2]) {
-    const bool up0 = bm[0] > m_ref[0] + up_raw;
-    const bool up1 = bm[1] > m_ref[1] + up_raw;
-    if (__any(up0 || up1)) {
-      const float n0 = up0 ? bm[0] : m_ref[0];
-      const float n1 = up1 ? bm[1] : m_ref[1];
-      const float a0 = up0 ? __builtin_amdgcn_exp2f((m_ref[0] - n0) * c) : 1.f;
-      const float a1 = up1 ? __builtin_amdgcn_exp2f((m_ref[1] - n1) * c) : 1.f;
-      m_ref[0] = n0;
-      m_ref[1] = n1;
-      osum[0] *= a0;
-      osum[1] *= a1;
+  auto rescale = [&](float bm) {
+    const bool up = bm > m_ref + up_raw;
+    if (__any(up)) {
+      const float mn = up ? bm : m_ref;
+      const float al = up ? __builtin_amdgcn_exp2f((m_ref - mn) * c) : 1.f;
+      m_ref = mn;
+      lsum *= al;
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        o[0][dt] *= a0;
-        o[1][dt] *= a1;
-      }
+      for (int dt = 0; dt < DT; ++dt) o[dt] *= al;
     }
   };
   // P = 2^(s c - m c) in bf16, packed as the B operand of the PV product:
-  // k-slot (q, e) is key q*4 + e (e < 4) or 16 + q*4 + (e - 4).
-  auto probs = [&](const f32x4 (&s)[2][2], bf16x8 (&pk)[2]) {
+  // slot e of k-step h is score register h*8 + e.
+  auto probs = [&](const f32x16 &s, bf16x8 (&pk)[2]) {
+    const float mc = m_ref * c;
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-      const float mc = m_ref[rb] * c;
+    for (int h = 0; h < 2; ++h) {
       u32x4 w;
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[rb][kt][0], c, -mc));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[rb][kt][1], c, -mc));
-        const float p2 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[rb][kt][2], c, -mc));
-        const float p3 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[rb][kt][3], c, -mc));
-        w[kt * 2 + 0] = pack_bf16x2(p0, p1);
-        w[kt * 2 + 1] = pack_bf16x2(p2, p3);
+      for (int e = 0; e < 4; ++e) {
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[h * 8 + 2 * e], c, -mc));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[h * 8 + 2 * e + 1], c, -mc));
+        const bf16x2 pp = __builtin_convertvector((f32x2{p0, p1}), bf16x2);
+        lsum = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, lsum, false);
+        w[e] = __builtin_bit_cast(uint32_t, pp);
       }
-      pk[rb] = __builtin_bit_cast(bf16x8, w);
+      pk[h] = __builtin_bit_cast(bf16x8, w);
     }
   };
-  // O^T += V^T P^T and the row sums.  The transposed read hands lane
-  // (q, j16) V[kbase + e][dt*16 + j16], e < 4.
+  // O^T += V^T P^T.
   auto pv = [&](const char *vst, const bf16x8 (&pk)[2]) {
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(vst + voff[dt]));
-      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(vst + voff[dt] + 16 * ROWB));
-      const bf16x8 vf = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      o[0][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pk[0], o[0][dt], 0, 0, 0);
-      o[1][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pk[1], o[1][dt], 0, 0, 0);
-    }
-    osum[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pk[0], osum[0], 0, 0, 0);
-    osum[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pk[1], osum[1], 0, 0, 0);
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(vst + voff[dt] + h * 16 * ROWB));
+        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(vst + voff8[dt] + h * 16 * ROWB));
+        const bf16x8 vf = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pk[h], o[dt], 0, 0, 0);
+      }
   };
 
-  f32x4 s[2][2];   // scores of the block whose PV product comes next
-  float bm[2];     // their row maxima
+  f32x16 s;        // scores of the block whose PV product comes next
+  float bm = 0.f;  // its row maximum
   // Prologue: wait for K0 (the eight later prologue loads may still fly),
   // then the scores of block 0.
   if (nb > 0) {
@@ -587,7 +567,7 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(TreeAttnArg
     if (wave_live) {
       scores(ring + 4 * 2 * BLK, s);
       if (n_full == 0) mask(s, 0);
-      rowmax(s, bm);
+      bm = rowmax(s);
     }
   }
 
@@ -636,16 +616,12 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(TreeAttnArg
       bf16x8 pk[2];
       probs(s, pk);
       if constexpr (kNext) {
-        f32x4 sn[2][2];
+        f32x16 sn;
         scores(cur, sn);
         pv(cur + BLK, pk);
         if constexpr (kMasked) mask(sn, j + 1);
-        rowmax(sn, bm);
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
-          s[rb][0] = sn[rb][0];
-          s[rb][1] = sn[rb][1];
-        }
+        bm = rowmax(sn);
+        s = sn;
       } else {
         pv(cur + BLK, pk);
       }
@@ -670,49 +646,31 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(TreeAttnArg
   for (; j + 1 < nb; ++j, cs = next_stage(cs)) step(j, cs, Yes{}, Yes{}, No{});     // block j+1 needs the mask
   if (nb > 0) step(nb - 1, cs, No{}, No{}, No{});
 
-  const int q4 = q * 4;
-  const float l_tot[2] = {osum[0][0], osum[1][0]};
-  if (chunks == 1) {
-    if (!wave_live) return;
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-      const int row = wrow0 + rb * 16 + j16;
-      if (row >= row_end) continue;
-      const float inv = l_tot[rb] > 0.f ? 1.f / l_tot[rb] : 0.f;
-      const int node = row / G, hh = row - (row / G) * G;
-      __bf16 *op = (__bf16 *)a.out + ((int64_t)(node_base + node) * a.num_q_heads + g * G + hh) * D + q4;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        u32x2 w;
-        w[0] = pack_bf16x2(o[rb][dt][0] * inv, o[rb][dt][1] * inv);
-        w[1] = pack_bf16x2(o[rb][dt][2] * inv, o[rb][dt][3] * inv);
-        *(u32x2 *)(op + dt * 16) = w;
-      }
-    }
-    return;
-  }
-
-  // ---- split prefix: write this chunk's partial: its own normalised output
-  // in bf16 (a weighted mean of V rows, so bf16 keeps 2^-9 relative
-  // precision), and its reference max and denominator in fp32;
-  // tree_attn_combine_kernel merges the chunks after this kernel.
   if (!wave_live) return;
+  const float l_tot = sum_over_halves(lsum);
+  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  // The row's normalised output in bf16: into `out`, or, when the prefix is
+  // split, as this chunk's partial (a weighted mean of V rows, so bf16 keeps
+  // 2^-9 relative precision) with its reference max and denominator in fp32;
+  // tree_attn_combine_kernel merges the chunks after this kernel.
+  const int64_t pslot = uid * kMaxRowsPerTile + (row - row0);
+  __bf16 *dst = chunks == 1 ? (__bf16 *)a.out + ((int64_t)(node_base + row_node) * a.num_q_heads + row_head) * D
+                            : a.ws_o + pslot * D;
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-    const int row = wrow0 + rb * 16 + j16;
-    if (row >= row_end) continue;
-    const int64_t slot = uid * kMaxRowsPerTile + (row - row0);
-    const float inv = l_tot[rb] > 0.f ? 1.f / l_tot[rb] : 0.f;
-    __bf16 *wo = a.ws_o + slot * D + q4;
+  for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      u32x2 w;
-      w[0] = pack_bf16x2(o[rb][dt][0] * inv, o[rb][dt][1] * inv);
-      w[1] = pack_bf16x2(o[rb][dt][2] * inv, o[rb][dt][3] * inv);
-      *(u32x2 *)(wo + dt * 16) = w;
+    for (int i = 0; i < 16; i += 8) {
+      // registers i .. i+3 / i+4 .. i+7 are columns i*2 + half*4 .. +3 and 8
+      // further; the halves swap so that each lane stores 16 contiguous bytes
+      const uint32_t x0 = pack_bf16x2(o[dt][i] * inv, o[dt][i + 1] * inv);
+      const uint32_t x1 = pack_bf16x2(o[dt][i + 2] * inv, o[dt][i + 3] * inv);
+      const uint32_t y0 = pack_bf16x2(o[dt][i + 4] * inv, o[dt][i + 5] * inv);
+      const uint32_t y1 = pack_bf16x2(o[dt][i + 6] * inv, o[dt][i + 7] * inv);
+      const auto r0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
+      const auto r1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
+      if (row_valid) *(u32x4 *)(dst + dt * 32 + i * 2 + half * 8) = u32x4{r0[0], r1[0], r0[1], r1[1]};
     }
-    if (lane < 16) *(f32x2 *)(a.ws_ml + slot * 2) = f32x2{m_ref[rb], l_tot[rb]};
-  }
+  if (chunks > 1 && row_valid && half == 0) *(f32x2 *)(a.ws_ml + pslot * 2) = f32x2{m_ref, l_tot};
 }
 
 // Merges the chunk partials of every split (request, kv-head, row tile):

@@ -144,6 +144,23 @@ def test_every_loop_boundary_of_the_step_pipeline(torch_cuda, tree):
     check_argmax_accept(b, amax, alen, tok, nodes)
 
 
+@pytest.mark.parametrize("head_dim,hq,hkv", [(128, 2, 2), (64, 2, 2), (128, 6, 2), (64, 22, 2)])
+def test_row_and_key_remainders(torch_cuda, head_dim, hq, hkv):
+    """Tree sizes around the 32-row wave and the 128-row tile (with 1, 3 and
+    11 query heads per kv-head), prefixes around the 32-key block, so waves end
+    part way through their rows and the last prefix and tree blocks part way
+    through both halves of a wave's keys.  Unit-variance inputs: the softmax is
+    far from uniform and its reference maximum moves."""
+    sizes = [1, 2, 3, 11, 21, 31, 32, 33, 43, 63, 64, 65, 95, 96, 97, 127, 128]
+    lens = [0, 1, 3, 4, 5, 8, 12, 16, 20, 28, 31, 32, 33, 36, 63, 65, 100]
+    rng = np.random.Generator(np.random.PCG64(hq + head_dim))
+    parents = [random_tree(rng, n, 12) for n in sizes]
+    b = make_batch(parents=parents, prefix_lens=lens, num_q_heads=hq, num_kv_heads=hkv, head_dim=head_dim,
+                   dtype="bf16", vocab=1000, seed=hq, qkv_std=1.0)
+    _, (out, *_) = run_device(b)
+    check_attention(b, out)
+
+
 def test_out_of_pool_pages_read_as_zero_pages(torch_cuda):
     """Block-table entries outside [0, num_pages) -- negative or past the pool
     -- act as all-zero pages: the call equals, bit for bit, the same batch
