@@ -226,9 +226,9 @@ int32_t adaserve_tree_accept(int32_t num_requests, int32_t total_nodes,
  * grid, by one argmax workgroup per node (they take the CUs no attention
  * work unit holds and the attention's tail, so the logits stream beside the
  * attention instead of after it); then the split-KV merge (when a prefix is
- * split) together with one acceptance wave per request.  F32 enqueues the
- * three calls' kernels one after another.  Calls that share a workspace
- * must not overlap in time.
+ * split) together with one acceptance wave per request.  F32 runs in two
+ * launches too (its prefixes are never split: the second is the acceptance
+ * alone).  Calls that share a workspace must not overlap in time.
  */
 int32_t adaserve_tree_verify_step(int32_t num_requests, const int32_t *node_indptr,
                                   const int32_t *node_indptr_host, const int32_t *parent,

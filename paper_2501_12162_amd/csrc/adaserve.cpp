@@ -220,19 +220,17 @@ int32_t tree_attn_verify_impl(int32_t num_requests, const int32_t *node_indptr, 
   a.row_groups = plan.row_groups;
   a.merge_blocks = plan.row_groups * (kMaxRowsPerTile / 16);
   a.stream_kv = plan.single_tile ? 1 : 0;
-  if (dtype == ADASERVE_BF16) {
-    PlanTable t;
-    fill_plan_table(t, num_requests, node_indptr_host, prefix_len_host, num_kv_heads, shape.group, plan);
-    a.plan_count = t.count;
-    if (t.count > 0) {
-      std::copy(t.entry, t.entry + t.count, a.plan);
-      a.merge_blocks = t.merge_blocks;
-    }
+  PlanTable t;
+  fill_plan_table(t, num_requests, node_indptr_host, prefix_len_host, num_kv_heads, shape.group, plan);
+  a.plan_count = t.count;
+  if (t.count > 0) {
+    std::copy(t.entry, t.entry + t.count, a.plan);
+    a.merge_blocks = t.merge_blocks;
   }
   a.sm_scale = sm_scale;
   a.scale_log2 = sm_scale * 1.4426950408889634f;
   hipStream_t s = (hipStream_t)stream;
-  if (step && dtype == ADASERVE_BF16) {
+  if (step) {
     a.logits = step->logits;
     a.logit_stride = step->row_stride;
     a.vocab = step->vocab;
@@ -244,22 +242,12 @@ int32_t tree_attn_verify_impl(int32_t num_requests, const int32_t *node_indptr, 
     a.accept_len = step->accept_len;
     a.accept_tokens = step->accept_tokens;
     a.accept_nodes = step->accept_nodes;
-    return launch_status(launch_verify_step_bf16(a, head_dim, plan.needs_combine, s), "verification step launch");
+    return launch_status(launch_verify_step(a, head_dim, dtype == ADASERVE_BF16, plan.needs_combine, s),
+                         "verification step launch");
   }
-  if (dtype == ADASERVE_BF16) {
-    st = launch_status(launch_tree_attn_bf16(a, head_dim, plan.needs_combine, s), "tree attention launch");
-  } else {
-    st = launch_status(launch_tree_attn_f32(a, head_dim, s), "tree attention launch");
-  }
-  if (st != ADASERVE_OK || !step) return st;
-  st = launch_status(launch_node_argmax(step->logits, step->row_stride, shape.total_nodes, step->vocab,
-                                        dtype == ADASERVE_BF16, step->target_argmax, s),
-                     "argmax launch");
-  if (st != ADASERVE_OK) return st;
-  return launch_status(launch_tree_accept(num_requests, shape.total_nodes, node_indptr, parent, step->draft_tokens,
-                                          step->target_argmax, step->max_accept, step->accept_len,
-                                          step->accept_tokens, step->accept_nodes, s),
-                       "accept launch");
+  if (dtype == ADASERVE_BF16)
+    return launch_status(launch_tree_attn_bf16(a, head_dim, plan.needs_combine, s), "tree attention launch");
+  return launch_status(launch_tree_attn_f32(a, head_dim, a.padded_grid, s), "tree attention launch");
 }
 
 }  // namespace

@@ -46,6 +46,20 @@ __device__ __forceinline__ float sum_over_halves(float v) {
   return __uint_as_float(a[0]) + __uint_as_float(a[1]);
 }
 
+// The same over lanes {l, l^16, l^32, l^48}: the four 16-lane rows of a wave
+// that hold the same column of a 16x16 MFMA result.
+__device__ __forceinline__ float max_over_lane_rows(float v) {
+  const uint32_t u = __float_as_uint(max_over_halves(v));
+  auto b = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __builtin_elementwise_maximum(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+__device__ __forceinline__ float sum_over_lane_rows(float v) {
+  const uint32_t u = __float_as_uint(sum_over_halves(v));
+  auto b = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 // Sum over all 64 lanes (every lane gets the total).
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

@@ -53,8 +53,8 @@ size_t round_up(size_t x, size_t a);
 // `units` holds (duration, count) pairs and is sorted in place.
 double lpt_makespan(std::vector<std::pair<double, int64_t>> &units);
 
-// Work plan of the bf16 kernel for a validated batch (host sizes only); an
-// empty plan (no units) for F32 or an empty batch.
+// Work plan of a validated batch (host sizes only); an empty plan (no units)
+// for an empty batch.  F32 plans split no prefix and need no workspace.
 AttnPlan make_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_host, int32_t hkv,
                    int32_t group, int32_t head_dim, int32_t dtype);
 

@@ -29,7 +29,7 @@ struct TreeAttnArgs {
   int32_t num_q_heads;
   int32_t num_kv_heads;
   int32_t group;               // Hq / Hkv
-  int32_t rows_per_tile;       // 64 or 128
+  int32_t rows_per_tile;       // 128 (F32: 16 or 32)
   int32_t chunk_target;        // batch-wide prefix chunk (chunk_keys() in plan.h), used when
   int32_t chunk_floor;         // minimum chunk in keys per tile row       plan_count == 0
   int64_t units;               // work units in the batch
@@ -41,7 +41,7 @@ struct TreeAttnArgs {
   // Fused verification step (adaserve_tree_verify_step; zero counts
   // otherwise): argmax_rows argmax workgroups follow the attention grid, and
   // acceptance waves for accept_requests requests follow the merge grid.
-  const void *logits;          // [argmax_rows, logit_stride] bf16
+  const void *logits;          // [argmax_rows, logit_stride], the attention's dtype
   int64_t logit_stride;
   int32_t vocab;
   int32_t argmax_rows;
@@ -60,12 +60,14 @@ struct TreeAttnArgs {
 hipError_t launch_tree_attn_bf16(TreeAttnArgs &a, int head_dim, bool needs_combine, hipStream_t stream);
 // The verification step in two launches: attention + argmax workgroups, then
 // the split-KV merge (when a prefix is split) + acceptance waves.
-hipError_t launch_verify_step_bf16(TreeAttnArgs &a, int head_dim, bool needs_combine, hipStream_t stream);
+hipError_t launch_verify_step(TreeAttnArgs &a, int head_dim, bool bf16, bool needs_combine, hipStream_t stream);
 // Device address of the static split-KV scratch array on the current device
 // (ADASERVE_TREE_ATTN_SCRATCH_BYTES bytes, 256-byte aligned); looked up once
 // per device.
 hipError_t tree_attn_scratch(void **out);
-hipError_t launch_tree_attn_f32(const TreeAttnArgs &a, int head_dim, hipStream_t stream);
+// `blocks` workgroups: the padded attention grid, and the argmax rows after it
+// in the verification step.
+hipError_t launch_tree_attn_f32(const TreeAttnArgs &a, int head_dim, int64_t blocks, hipStream_t stream);
 
 hipError_t launch_node_argmax(const void *logits, int64_t row_stride, int32_t rows, int32_t vocab,
                               bool bf16, int32_t *out, hipStream_t stream);

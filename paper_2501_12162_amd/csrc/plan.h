@@ -17,6 +17,9 @@
 // `floor_mult` * rows keys (the planner picks 8, 16 or 32); above that
 // floor the batch-wide `chunk_target` sets the split.
 //
+// The F32 kernel takes the same units with 16- or 32-row tiles and every
+// prefix whole (kF32Chunk).
+//
 // Units are numbered request by request; inside a request the order is
 // (chunk, g, tile) with the tile fastest, so the tiles that read the same KV
 // chunk are neighbours (and mostly land on one XCD, see xcd_swizzle), and
@@ -57,6 +60,8 @@ ADASERVE_HD int32_t chunk_keys(int32_t n_nodes, int32_t group, int32_t rows_per_
   while (c < floor_mult * rows && c < kMaxChunk) c *= 2;
   return c > chunk_target ? c : chunk_target;
 }
+
+constexpr int kF32Chunk = 1 << 23;    // longer than any prefix: F32 units are never split
 
 ADASERVE_HD int32_t prefix_chunks(int32_t prefix_len, int32_t chunk) {
   return prefix_len > 0 ? ceil_div(prefix_len, chunk) : 1;

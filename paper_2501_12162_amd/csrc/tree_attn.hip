@@ -38,6 +38,8 @@
 //    denominator in fp32) and a second, fully parallel kernel merges them
 //    (the kernel boundary makes the partials of every XCD visible without
 //    per-workgroup cache flushes).
+#include <float.h>
+
 #include <mutex>
 #include <type_traits>
 
@@ -53,6 +55,7 @@ namespace adaserve {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kWavesF32 = 8;   // of an F32 workgroup
 
 // 16 bytes of zeros: the source of every DMA lane whose key is out of range,
 // so no NaN from an unused page slot reaches LDS.  Its device address is
@@ -175,8 +178,77 @@ __device__ bool locate_request(int64_t idx, bool count_groups, const TreeAttnArg
   return false;
 }
 
+// The work unit with logical id `uid`: its request, that request's sizes, the
+// prefix keys per unit and the request's first unit id.  From the plan table
+// in the kernel arguments, or, without one, by the scan.  Every field is
+// uniform; false when there is no such unit or its request does not fit the
+// batch.
+struct Unit {
+  int32_t r, node_base, n, L, chunk_len;
+  int64_t ubase;
+};
+__device__ __forceinline__ bool find_unit(const TreeAttnArgs &a, int64_t uid, Unit &u) {
+  int32_t r, node_base, n, L, chunk_len;
+  int64_t ubase;
+  if (a.plan_count > 0) {
+    // the dispatch-ordered plan in the kernel arguments
+    const int lo = __builtin_amdgcn_readfirstlane(find_plan_entry(a, uid, false));
+    if (lo < 0) return false;
+    r = plan_request(a.plan[lo].request_and_chunk);
+    chunk_len = plan_chunk_keys(a.plan[lo].request_and_chunk);
+    ubase = lo > 0 ? a.plan[lo - 1].unit_end : 0;
+    node_base = a.plan[lo].node_base;
+    n = plan_nodes(a.plan[lo].n_and_len);
+    L = plan_prefix_len(a.plan[lo].n_and_len);
+  } else {
+    int64_t gbase;
+    if (!locate_request(uid, false, a, r, ubase, gbase)) return false;
+    node_base = a.node_indptr[r];
+    n = min(max(a.node_indptr[r + 1] - node_base, 0), kMaxTreeNodes);
+    L = max(a.prefix_len[r], 0);
+    chunk_len = chunk_keys(n, a.group, a.rows_per_tile, a.chunk_target, a.chunk_floor);
+  }
+  // Request values are uniform; make that visible so branches on them stay scalar.
+  u.r = __builtin_amdgcn_readfirstlane(r);
+  u.node_base = __builtin_amdgcn_readfirstlane(node_base);
+  u.n = __builtin_amdgcn_readfirstlane(n);
+  u.L = __builtin_amdgcn_readfirstlane(L);
+  u.chunk_len = __builtin_amdgcn_readfirstlane(chunk_len);
+  u.ubase = ((int64_t)__builtin_amdgcn_readfirstlane((int32_t)(ubase >> 32)) << 32) |
+            (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)ubase);
+  return u.n > 0 && u.node_base >= 0 && u.node_base + u.n <= a.total_nodes;
+}
+
 __device__ __forceinline__ uint32_t set_bit_in(uint32_t w, int word, int v) {
   return ((v >> 5) == word) ? (w | (1u << (v & 31))) : w;
+}
+
+// Ancestor sets of a request's n nodes from its parents in LDS: bit j of
+// node i's 128-bit set is 1 when j is on i's root-to-node path, i included.
+// The walk stops at anything that is not a parent strictly before its child,
+// so malformed trees stay in bounds.  Called by all of the workgroup's
+// `threads` threads.
+__device__ __forceinline__ void build_ancestors(const int32_t *par, uint32_t *anc, int n, int threads) {
+  for (int i = threadIdx.x; i < kMaxTreeNodes; i += threads) {
+    uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
+    if (i < n) {
+      int v = i;
+      for (int step = 0; step < kMaxTreeNodes; ++step) {
+        w0 = set_bit_in(w0, 0, v);
+        w1 = set_bit_in(w1, 1, v);
+        w2 = set_bit_in(w2, 2, v);
+        w3 = set_bit_in(w3, 3, v);
+        if (v == 0) break;
+        const int p = par[v];
+        if (p < 0 || p >= v) break;
+        v = p;
+      }
+    }
+    anc[i * 4 + 0] = w0;
+    anc[i * 4 + 1] = w1;
+    anc[i * 4 + 2] = w2;
+    anc[i * 4 + 3] = w3;
+  }
 }
 
 // 16-byte chunk permutation of LDS row `row`: chunk c of the row is stored in
@@ -227,35 +299,9 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(TreeAttnArg
   }
   const int64_t uid = xcd_swizzle(blockIdx.x, a.padded_grid);
   if (uid >= a.units) return;
-  int32_t r, node_base, n, L, chunk_len;
-  int64_t ubase;
-  if (a.plan_count > 0) {
-    // the dispatch-ordered plan in the kernel arguments
-    const int lo = __builtin_amdgcn_readfirstlane(find_plan_entry(a, uid, false));
-    if (lo < 0) return;
-    r = plan_request(a.plan[lo].request_and_chunk);
-    chunk_len = plan_chunk_keys(a.plan[lo].request_and_chunk);
-    ubase = lo > 0 ? a.plan[lo - 1].unit_end : 0;
-    node_base = a.plan[lo].node_base;
-    n = plan_nodes(a.plan[lo].n_and_len);
-    L = plan_prefix_len(a.plan[lo].n_and_len);
-  } else {
-    int64_t gbase;
-    if (!locate_request(uid, false, a, r, ubase, gbase)) return;
-    node_base = a.node_indptr[r];
-    n = min(max(a.node_indptr[r + 1] - node_base, 0), kMaxTreeNodes);
-    L = max(a.prefix_len[r], 0);
-    chunk_len = chunk_keys(n, a.group, a.rows_per_tile, a.chunk_target, a.chunk_floor);
-  }
-  // Request values are uniform; make that visible so branches on them stay scalar.
-  r = __builtin_amdgcn_readfirstlane(r);
-  node_base = __builtin_amdgcn_readfirstlane(node_base);
-  n = __builtin_amdgcn_readfirstlane(n);
-  L = __builtin_amdgcn_readfirstlane(L);
-  chunk_len = __builtin_amdgcn_readfirstlane(chunk_len);
-  ubase = ((int64_t)__builtin_amdgcn_readfirstlane((int32_t)(ubase >> 32)) << 32) |
-          (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)ubase);
-  if (n == 0 || node_base < 0 || node_base + n > a.total_nodes) return;
+  Unit unit;
+  if (!find_unit(a, uid, unit)) return;
+  const int32_t r = unit.r, node_base = unit.node_base, n = unit.n, L = unit.L, chunk_len = unit.chunk_len;
   // a chunk is whole 32-key blocks and its page ids fit the page-id registers
   if (chunk_len <= 0 || chunk_len > kMaxChunk || chunk_len % kKeysPerBlock != 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -264,7 +310,7 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(TreeAttnArg
   const int RT = a.rows_per_tile;
   const int32_t tiles = row_tiles(n, G, RT);
   const int32_t chunks = prefix_chunks(L, chunk_len);
-  const int64_t u = uid - ubase;
+  const int64_t u = uid - unit.ubase;
   const int32_t tile = (int32_t)(u % tiles);
   const int64_t rest = u / tiles;
   const int32_t g = (int32_t)(rest % a.num_kv_heads);
@@ -414,32 +460,8 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(TreeAttnArg
     issue_v(ring + 3 * 2 * BLK, 3, pg3);
   }
 
-  // Ancestor sets (while the first blocks are in flight): bit j of node i's
-  // set is 1 when j is on i's root-to-node path, i included.  The walk stops
-  // at anything that is not a parent strictly before its child, so malformed
-  // trees stay in bounds.
-  if (last_chunk) {
-    for (int i = tid; i < kMaxTreeNodes; i += kThreads) {
-      uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
-      if (i < n) {
-        int v = i;
-        for (int step = 0; step < kMaxTreeNodes; ++step) {
-          w0 = set_bit_in(w0, 0, v);
-          w1 = set_bit_in(w1, 1, v);
-          w2 = set_bit_in(w2, 2, v);
-          w3 = set_bit_in(w3, 3, v);
-          if (v == 0) break;
-          const int p = par[v];
-          if (p < 0 || p >= v) break;
-          v = p;
-        }
-      }
-      anc[i * 4 + 0] = w0;
-      anc[i * 4 + 1] = w1;
-      anc[i * 4 + 2] = w2;
-      anc[i * 4 + 3] = w3;
-    }
-  }
+  // Ancestor sets, while the first blocks are in flight.
+  if (last_chunk) build_ancestors(par, anc, n, kThreads);
 
   // Per-lane LDS offsets of the MFMA operand fragments inside a stage.
   const int half = lane >> 5;
@@ -779,151 +801,306 @@ __global__ __launch_bounds__(kThreads) void tree_attn_combine_kernel(TreeAttnArg
   }
 }
 
-// fp32 path: one workgroup per (node, q-head), exact fp32 arithmetic on the
-// vector ALUs (small shapes; the matrix cores have no fp32 input path that
-// keeps full precision for Q.K).  The node's keys -- its prefix, then its
-// root path -- are taken in chunks of 1024: every thread scores whole keys
-// (a dot product over the head dim), the chunk's softmax weights go to LDS,
-// then thread (group g, column d) accumulates column d of the weighted
-// values over every G-th key; an online softmax joins the chunks.
-template <int D>
-__global__ __launch_bounds__(256) void tree_attn_f32_kernel(TreeAttnArgs a) {
-  constexpr int kT = 256;
-  constexpr int G = kT / D;       // key groups of the value accumulation
-  constexpr int CH = 1024;        // keys per chunk
-  __shared__ float qs[D];
-  __shared__ float ps[CH];
-  __shared__ int64_t rowoff[CH];  // >= 0: element offset in the page pool; -1: zero key; <= -2: tree row
-  __shared__ int32_t path[kMaxTreeNodes];
-  __shared__ float red[kT / 64];
-  __shared__ float part[kT];
-  __shared__ int32_t info[4];     // request, node base, path length, ok
-  const int64_t idx = blockIdx.x;
-  const int32_t node = (int32_t)(idx / a.num_q_heads);
-  const int32_t h = (int32_t)(idx % a.num_q_heads);
-  if (node >= a.total_nodes) return;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  if (t == 0) {
-    // request owning this node, then the node's root path
-    int lo = 0, hi = a.num_requests - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (a.node_indptr[mid] <= node) lo = mid; else hi = mid - 1;
+// fp32 path: one workgroup of 8 waves per (request, kv-head, tile of 16 RB
+// rows), rows as in the bf16 kernel.  The unit's keys -- the prefix's 16-key
+// pages, then the tree in 16-node blocks -- are cut into 8 contiguous runs,
+// one per wave, and the waves' online softmaxes are joined through LDS at the
+// end.  S^T = K Q^T and O^T = V^T P^T run on v_mfma_f32_16x16x4_f32 (fp32
+// inputs, products and sums).  Both contractions may take their slots in any
+// order, so they are ordered such that every lane loads 16 contiguous bytes
+// of K and of V straight into the operand registers and P needs no exchange:
+// contraction slot q of QK step (c, e) is head-dim element 16 c + 4 q + e,
+// slot q of PV step e is key 4 q + e, and O^T tile (h, k) holds the head-dim
+// columns 64 h + 4 j + k, j = 0 .. 15.
+// What bounds it: the matrix cores of the CUs that hold the longest requests
+// (a unit's keys stay on one CU: F32 calls have no workspace for partial
+// results).  So small batches take 16-row tiles (RB = 1), which put more CUs
+// to work, and batches that fill the chip with 32-row tiles (RB = 2) take
+// those, which read each K/V byte half as often.  4 requests of 15-55 nodes
+// over 147-1254 keys (16 / 4 heads, D = 128): 41 us, of which the longest
+// units' matrix instructions are 19 and launch, start and merge 13; a
+// workgroup per (node, q-head) with the products on the vector ALUs read the
+// whole prefix once for each and took 266.  One request of 16 nodes over 256
+// keys (8 / 8 heads, D = 64): 14.8 -> 10 us.  A second set of K and V registers
+// (loads two blocks ahead) and 12 or 16 waves with one set measured no faster.
+template <int D, int RB>
+__global__ __launch_bounds__(kWavesF32 * 64) void tree_attn_f32_kernel(TreeAttnArgs a) {
+  constexpr int NW = kWavesF32, kT = NW * 64;
+  constexpr int RT = 16 * RB;
+  constexpr int NC = D / 16;      // 16-byte K loads per lane and block
+  constexpr int NH = D / 64;      // 16-byte V loads per lane and key
+  constexpr int LDO = D + 4;      // row stride of the waves' outputs in LDS (spreads a column over the banks)
+  __shared__ __align__(16) float mo[NW * RT * LDO];
+  __shared__ float mw[NW][RT], lw[NW][RT];
+  static_assert(kMaxTreeNodes <= RT * LDO, "a wave's parents fit in its part of mo");
+
+  if ((int64_t)blockIdx.x >= a.padded_grid) {
+    // fused verification step: argmax workgroups follow the attention units
+    const int64_t row = (int64_t)blockIdx.x - a.padded_grid;
+    if (row < a.argmax_rows)
+      argmax_row<false, kT>(a.logits, a.logit_stride, a.vocab, (int32_t)row, a.argmax_out, mo, (int *)(mo + 64));
+    return;
+  }
+  const int64_t uid = xcd_swizzle(blockIdx.x, a.padded_grid);
+  if (uid >= a.units) return;
+  Unit unit;
+  if (!find_unit(a, uid, unit)) return;
+  const int32_t r = unit.r, node_base = unit.node_base, n = unit.n, L = unit.L;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = lane >> 4, j = lane & 15;
+  const int G = a.group;
+  const int32_t tiles = row_tiles(n, G, RT);
+  const int64_t u = uid - unit.ubase;
+  const int32_t row0 = (int32_t)(u % tiles) * RT;
+  const int32_t g = (int32_t)(u / tiles);
+  const int32_t M = n * G;
+  if (g >= a.num_kv_heads) return;
+
+  // this wave's blocks of 16 keys
+  const int32_t n_prefix_blocks = ceil_div(L, kPageSize);
+  const int32_t nb = n_prefix_blocks + ceil_div(n, 16);
+  const int32_t b0 = (int32_t)((int64_t)nb * wave / NW), b1 = (int32_t)((int64_t)nb * (wave + 1) / NW);
+
+  // The waves that have tree blocks fetch the parents (each into its part of
+  // mo, which holds nothing else before the merge).
+  const bool has_tree = b1 > n_prefix_blocks && b1 > b0;
+  int32_t *const par = (int32_t *)(mo + wave * RT * LDO);
+  if (has_tree)
+    for (int i = lane; i < n; i += 64) par[i] = a.parent[node_base + i];
+
+  // query fragments: lane holds row j of each 16-row block
+  f32x4 qf[RB][NC];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int row = row0 + rb * 16 + j;
+    const int node = row < M ? row / G : 0, hh = row < M ? row - node * G : 0;
+    const float *qp = (const float *)a.q + ((int64_t)(node_base + node) * a.num_q_heads + g * G + hh) * D + q * 4;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) qf[rb][c] = *(const f32x4 *)(qp + c * 16);
+  }
+
+  // Block b's page (-1: the tree, an entry past the block-table row, or a page
+  // id outside the pool) and the addresses of its rows.  Lane i holds the page
+  // of block page_base + i; blocks are asked for in ascending order.  (A load
+  // per block would be waited for, and every K and V load in flight with it.)
+  int32_t page_base = b0, pages = -1;
+  auto load_pages = [&]() {
+    const int b = page_base + lane;
+    pages = -1;
+    if (b < n_prefix_blocks && b < a.bt_stride) {
+      const int32_t p = a.block_table[(int64_t)r * a.bt_stride + b];
+      if (p >= 0 && p < a.num_pages) pages = p;
     }
-    const int32_t base = a.node_indptr[lo];
-    const int32_t n = a.node_indptr[lo + 1] - base;
-    int ok = node >= base && node < base + n && n <= kMaxTreeNodes;
-    int len = 0;
-    if (ok) {
-      int v = node - base;
+  };
+  load_pages();
+  auto page_of = [&](int b) -> int32_t {
+    if (b >= page_base + 64) {
+      page_base = b;
+      load_pages();
+    }
+    return __builtin_amdgcn_readlane(pages, b - page_base);
+  };
+  const int64_t tree_stride = (int64_t)a.num_kv_heads * D;
+  auto rows_at = [&](const void *pool, const void *tree, int b, int32_t page, int64_t &stride, int &rows) {
+    if (b < n_prefix_blocks && page >= 0) {
+      stride = D;
+      rows = min(kPageSize, L - b * kPageSize);
+      return (const float *)pool + ((int64_t)page * a.num_kv_heads + g) * kPageSize * D;
+    }
+    // a page outside the pool reads tree rows, whose values are not used
+    const int tb = b < n_prefix_blocks ? 0 : b - n_prefix_blocks;
+    stride = tree_stride;
+    rows = min(16, n - tb * 16);
+    return (const float *)tree + ((int64_t)(node_base + tb * 16) * a.num_kv_heads + g) * D;
+  };
+  // Rows past the block's keys repeat its last one (their scores are masked,
+  // their V is zeroed), so every block loads without branches.
+  f32x4 kr[NC], vr[4][NH];
+  auto load_k = [&](int b, int32_t page) {
+    int64_t stride;
+    int rows;
+    const float *base = rows_at(a.k_pages, a.k_tree, b, page, stride, rows);
+    const float *p = base + min(j, rows - 1) * stride + q * 4;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) kr[c] = *(const f32x4 *)(p + c * 16);
+  };
+  auto load_v = [&](int b, int32_t page) {
+    int64_t stride;
+    int rows;
+    const float *base = rows_at(a.v_pages, a.v_tree, b, page, stride, rows);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+        vr[e][h] = *(const f32x4 *)(base + min(q * 4 + e, rows - 1) * stride + h * 64 + j * 4);
+  };
+
+  f32x4 o[RB][NH][4];
+  float m[RB], l[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    m[rb] = -FLT_MAX;
+    l[rb] = 0.f;
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[rb][h][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  int32_t page = -1;   // of the block in kr / vr
+  if (b0 < b1) {
+    page = page_of(b0);
+    load_k(b0, page);
+    load_v(b0, page);
+  }
+  // The ancestor sets of the lane's rows' nodes, while the first block's loads
+  // are in flight: bit i is 1 when node i is on the root-to-node path.  The
+  // walk stops at anything that is not a parent strictly before its child.
+  uint32_t an[RB][4];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) an[rb][0] = an[rb][1] = an[rb][2] = an[rb][3] = 0;
+  if (has_tree) {
+    wave_lds_sync();
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      int v = min((row0 + rb * 16 + j) / G, n - 1);
       for (int step = 0; step < kMaxTreeNodes; ++step) {
-        path[len++] = v;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) an[rb][w] = set_bit_in(an[rb][w], w, v);
         if (v == 0) break;
-        const int p = a.parent[base + v];
+        const int p = par[v];
         if (p < 0 || p >= v) break;
         v = p;
       }
     }
-    info[0] = lo;
-    info[1] = base;
-    info[2] = len;
-    info[3] = ok;
   }
-  const int g = h / a.group;
-  const float *q = (const float *)a.q + ((int64_t)node * a.num_q_heads + h) * D;
-  for (int d = t; d < D; d += kT) qs[d] = q[d];
-  __syncthreads();
-  if (!info[3]) return;
-  const int r = info[0], base = info[1], npath = info[2];
-  const int32_t L = max(a.prefix_len[r], 0);
-  const int32_t nkeys = L + npath;
-  const float *kp = (const float *)a.k_pages, *vp = (const float *)a.v_pages;
-  const float *kt = (const float *)a.k_tree, *vt = (const float *)a.v_tree;
-  const int col = t % D, grp = t / D;
-  float m = -INFINITY, l = 0.f, acc = 0.f;
-  for (int32_t k0 = 0; k0 < nkeys; k0 += CH) {
-    const int n = min(CH, nkeys - k0);
-    float cmax = -INFINITY;
-    for (int j = t; j < n; j += kT) {
-      const int32_t key = k0 + j;
-      int64_t off;
-      const float *kr;
-      if (key < L) {
-        const int32_t e = key / kPageSize;
-        const int32_t pg = e < a.bt_stride ? a.block_table[(int64_t)r * a.bt_stride + e] : -1;
-        off = (pg < 0 || pg >= a.num_pages) ? -1
-              : (((int64_t)pg * a.num_kv_heads + g) * kPageSize + key % kPageSize) * D;
-        kr = off >= 0 ? kp + off : nullptr;
-      } else {
-        const int64_t toff = ((int64_t)(base + path[key - L]) * a.num_kv_heads + g) * D;
-        off = -2 - toff;
-        kr = kt + toff;
-      }
-      float sc = 0.f;
-      if (kr) {
+
+  // The next block's K and V replace this one's as soon as they are used
+  // (past the last block the last one is loaded again).
+  for (int b = b0; b < b1; ++b) {
+    const int bn = min(b + 1, b1 - 1);
+    const int32_t page_next = page_of(bn);
+    f32x4 s[RB];
 #pragma unroll
-        for (int d = 0; d < D; d += 4) {
-          const f32x4 kv = *(const f32x4 *)(kr + d);
-          sc = fmaf(qs[d], kv[0], sc);
-          sc = fmaf(qs[d + 1], kv[1], sc);
-          sc = fmaf(qs[d + 2], kv[2], sc);
-          sc = fmaf(qs[d + 3], kv[3], sc);
-        }
-      }
-      sc *= a.sm_scale;
-      ps[j] = sc;
-      rowoff[j] = off;
-      cmax = fmaxf(cmax, sc);
-    }
+    for (int rb = 0; rb < RB; ++rb) s[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, o, 64));
-    if (lane == 0) red[wave] = cmax;
-    __syncthreads();
-    float mn = m;
+    for (int c = 0; c < NC; ++c)
 #pragma unroll
-    for (int w = 0; w < kT / 64; ++w) mn = fmaxf(mn, red[w]);
-    __syncthreads();
-    const float alpha = m > -INFINITY ? expf(m - mn) : 0.f;
-    float lsum = 0.f;
-    for (int j = t; j < n; j += kT) {
-      const float p = expf(ps[j] - mn);
-      ps[j] = p;
-      lsum += p;
-    }
-    lsum = wave_sum(lsum);
-    if (lane == 0) red[wave] = lsum;
-    __syncthreads();
-    float csum = 0.f;
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
-    for (int w = 0; w < kT / 64; ++w) csum += red[w];
-    l = l * alpha + csum;
-    acc *= alpha;
-    m = mn;
-    if (grp < G)
-      for (int j0 = grp; j0 < n; j0 += 8 * G) {
-        // eight keys' loads in flight before their products
-        float pv[8], vv[8];
+        for (int rb = 0; rb < RB; ++rb)
+          s[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[c][e], qf[rb][c][e], s[rb], 0, 0, 0);
+    load_k(bn, page_next);
+
+    // s[rb][e]: key 4 q + e of the block, row j
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int j = j0 + u * G;
-          const int64_t off = j < n ? rowoff[j] : -1;
-          const float *src = off >= 0 ? vp + off + col : off == -1 ? vt + col : vt + (-2 - off) + col;
-          pv[u] = j < n && off != -1 ? ps[j] : 0.f;
-          vv[u] = *src;  // a zero row reads tree row 0 and weighs it 0 below
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[rb][e] *= a.sm_scale;
+    const bool prefix = b < n_prefix_blocks;
+    const int tb = b - n_prefix_blocks;
+    const int valid = prefix ? min(kPageSize, L - b * kPageSize) : min(16, n - tb * 16);
+    const bool zero_page = prefix && page < 0;
+    if (!prefix || valid < 16 || zero_page) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        uint32_t seen = 0xffffu;
+        if (!prefix) {
+          const uint32_t w0 = an[rb][0], w1 = an[rb][1], w2 = an[rb][2], w3 = an[rb][3];
+          const uint32_t w = (tb & 4) ? ((tb & 2) ? w3 : w2) : ((tb & 2) ? w1 : w0);
+          seen = (tb & 1) ? w >> 16 : w;
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc = pv[u] != 0.f ? fmaf(pv[u], vv[u], acc) : acc;
+        for (int e = 0; e < 4; ++e) {
+          const int key = q * 4 + e;
+          const float x = zero_page ? 0.f : s[rb][e];
+          s[rb][e] = key < valid && ((seen >> key) & 1u) ? x : -INFINITY;
+        }
       }
-    __syncthreads();  // ps, rowoff and red are rewritten by the next chunk
-  }
-  part[t] = acc;
-  __syncthreads();
-  if (t < D) {
-    float o = 0.f;
 #pragma unroll
-    for (int k = 0; k < G; ++k) o += part[k * D + t];
-    float *out = (float *)a.out + ((int64_t)node * a.num_q_heads + h) * D;
-    out[t] = l > 0.f ? o / l : 0.f;
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+          if (zero_page || q * 4 + e >= valid) vr[e][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    float mn[RB];
+    bool up = false;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const float bm = max_over_lane_rows(__builtin_elementwise_maximum(__builtin_elementwise_maximum(s[rb][0], s[rb][1]),
+                                                                        __builtin_elementwise_maximum(s[rb][2], s[rb][3])));
+      mn[rb] = bm > m[rb] ? bm : m[rb];
+      up |= bm > m[rb];
+    }
+    if (__any(up)) {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        const float al = expf(m[rb] - mn[rb]);
+        m[rb] = mn[rb];
+        l[rb] *= al;
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[rb][h][i] *= al;
+      }
+    }
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s[rb][e] = expf(s[rb][e] - m[rb]);
+        l[rb] += s[rb][e];
+      }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb)
+            o[rb][h][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[e][h][i], s[rb][e], o[rb][h][i], 0, 0, 0);
+    load_v(bn, page_next);
+    page = page_next;
+  }
+
+  // The waves' (max, sum, output) to LDS, then the merge.
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int rl = rb * 16 + j;
+    const float ls = sum_over_lane_rows(l[rb]);
+    if (q == 0) {
+      mw[wave][rl] = m[rb];
+      lw[wave][rl] = ls;
+    }
+    float *dst = mo + (wave * RT + rl) * LDO;
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *(f32x4 *)(dst + h * 64 + q * 16 + i * 4) =
+            f32x4{o[rb][h][0][i], o[rb][h][1][i], o[rb][h][2][i], o[rb][h][3][i]};
+  }
+  __syncthreads();
+  for (int it = tid; it < RT * (D / 4); it += kT) {
+    const int rl = it / (D / 4), col = it % (D / 4) * 4;
+    const int row = row0 + rl;
+    if (row >= M) continue;
+    float mm = mw[0][rl];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mm = fmaxf(mm, mw[w][rl]);
+    float den = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float wt = expf(mw[w][rl] - mm);
+      den += wt * lw[w][rl];
+      acc += *(const f32x4 *)(mo + (w * RT + rl) * LDO + col) * wt;
+    }
+    const int node = row / G, hh = row - node * G;
+    f32x4 res = {0.f, 0.f, 0.f, 0.f};
+    if (den > 0.f) res = acc / den;
+    *(f32x4 *)((float *)a.out + ((int64_t)(node_base + node) * a.num_q_heads + g * G + hh) * D + col) = res;
   }
 }
 
@@ -1007,15 +1184,34 @@ hipError_t launch_tree_attn_bf16(TreeAttnArgs &a, int head_dim, bool needs_combi
   return hipGetLastError();
 }
 
-hipError_t launch_verify_step_bf16(TreeAttnArgs &a, int head_dim, bool needs_combine, hipStream_t stream) {
+template <int D, int RB>
+static void launch_f32_tile(const TreeAttnArgs &a, int64_t blocks, hipStream_t stream) {
+  hipLaunchKernelGGL((tree_attn_f32_kernel<D, RB>), dim3((unsigned)blocks), dim3(kWavesF32 * 64), 0, stream, a);
+}
+
+hipError_t launch_tree_attn_f32(const TreeAttnArgs &a, int head_dim, int64_t blocks, hipStream_t stream) {
+  if (blocks == 0) return hipSuccess;
+  const bool wide = a.rows_per_tile == 32;
+  if (head_dim == 128)
+    wide ? launch_f32_tile<128, 2>(a, blocks, stream) : launch_f32_tile<128, 1>(a, blocks, stream);
+  else
+    wide ? launch_f32_tile<64, 2>(a, blocks, stream) : launch_f32_tile<64, 1>(a, blocks, stream);
+  return hipGetLastError();
+}
+
+hipError_t launch_verify_step(TreeAttnArgs &a, int head_dim, bool bf16, bool needs_combine, hipStream_t stream) {
   hipError_t e = zero16_address(&a.zero16);
   if (e != hipSuccess) return e;
   const dim3 block(kThreads);
   const int64_t g1 = (a.units > 0 ? a.padded_grid : 0) + a.argmax_rows;
   if (a.units == 0) a.padded_grid = 0;
   if (g1 > 0) {
-    launch_attention(a, head_dim, g1, stream);
-    e = hipGetLastError();
+    if (bf16) {
+      launch_attention(a, head_dim, g1, stream);
+      e = hipGetLastError();
+    } else {
+      e = launch_tree_attn_f32(a, head_dim, g1, stream);
+    }
     if (e != hipSuccess) return e;
   }
   if (!needs_combine) a.merge_blocks = 0;
@@ -1025,17 +1221,6 @@ hipError_t launch_verify_step_bf16(TreeAttnArgs &a, int head_dim, bool needs_com
     hipLaunchKernelGGL(tree_attn_combine_kernel<128>, dim3((unsigned)g2), block, 0, stream, a);
   else
     hipLaunchKernelGGL(tree_attn_combine_kernel<64>, dim3((unsigned)g2), block, 0, stream, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_tree_attn_f32(const TreeAttnArgs &a, int head_dim, hipStream_t stream) {
-  const int64_t blocks = (int64_t)a.total_nodes * a.num_q_heads;
-  if (blocks == 0) return hipSuccess;
-  const dim3 grid((unsigned)blocks), block(256);
-  if (head_dim == 128)
-    hipLaunchKernelGGL(tree_attn_f32_kernel<128>, grid, block, 0, stream, a);
-  else
-    hipLaunchKernelGGL(tree_attn_f32_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();
 }
 

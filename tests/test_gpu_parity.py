@@ -161,6 +161,36 @@ def test_row_and_key_remainders(torch_cuda, head_dim, hq, hkv):
     check_attention(b, out)
 
 
+@pytest.mark.parametrize("head_dim,hq,hkv,repeat", [(64, 2, 2, 1), (128, 6, 2, 1), (64, 22, 2, 9), (128, 16, 4, 12)])
+def test_f32_row_and_key_remainders(torch_cuda, head_dim, hq, hkv, repeat):
+    """The fp32 kernel around its 16- and 32-row tiles (repeat > 1: enough rows
+    for the 32-row ones, and past the plan table with 180 requests), its 16-key
+    blocks and its 8 waves' key runs, with an out-of-pool page in one prefix
+    and deep chains.  An output is a weighted mean of values below 5 whose
+    weights' exponents carry at most D sums of products below 2^5, each off by
+    2^-24: 128 * 2^5 * 2^-24 / sqrt(D) * 5 < 2e-4 at worst and about its square
+    root of the count, 2e-5, when the signs are random."""
+    sizes = [1, 2, 3, 5, 8, 15, 16, 17, 31, 32, 33, 63, 65, 127, 128] * repeat
+    lens = [0, 1, 3, 15, 16, 17, 31, 33, 127, 128, 129, 144, 300, 1100, 40] * repeat
+    rng = np.random.Generator(np.random.PCG64(hq + head_dim))
+    parents = [chain_tree(n) if n % 2 else random_tree(rng, n, 12) for n in sizes]
+    b = make_batch(parents=parents, prefix_lens=lens, num_q_heads=hq, num_kv_heads=hkv, head_dim=head_dim,
+                   dtype="f32", vocab=64, seed=hq)
+    zero = np.zeros((1,) + b.k_pages.shape[1:], dtype=np.float32)
+    b.k_pages, b.v_pages = np.concatenate([b.k_pages, zero]), np.concatenate([b.v_pages, zero])
+    last = b.num_pages - 1
+    b.block_table[12, [0, 7]] = last           # the oracle reads a zero page
+    d, _ = run_device(b)
+    assert d.workspace_bytes == 0
+    d.block_table[12, 0], d.block_table[12, 7] = -1, last + 5   # the kernel entries outside the pool
+    d.out.fill_(float("nan"))
+    d.attention()
+    out = d.results()[0]
+    ref = oracle.tree_attn_batch(b)
+    assert np.isfinite(out).all()
+    assert float(np.abs(out - ref).max()) <= 2e-5
+
+
 def test_out_of_pool_pages_read_as_zero_pages(torch_cuda):
     """Block-table entries outside [0, num_pages) -- negative or past the pool
     -- act as all-zero pages: the call equals, bit for bit, the same batch
