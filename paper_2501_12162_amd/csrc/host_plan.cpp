@@ -67,16 +67,40 @@ int32_t validate_attn_shape(int32_t num_requests, const int32_t *indptr_host, co
 
 
 
-// Cost model of the bf16 kernel, measured on MI355X: paged K/V streaming
-// over the whole chip; one 32-key pipeline step of a workgroup while two
-// workgroups share each CU (it hardly depends on the tile's row count: the
-// four waves compute their row blocks side by side); the fixed cost of a
-// unit (first loads of the block table, queries and K block 0, then the
-// output writes); and the latency the combine kernel adds.
+// Cost model of the bf16 kernel, measured on MI355X.
+//  * A call costs kCallUs around its steps (launch, start-up loads, output
+//    writes) and kCombineUs when a prefix is split (the merge).
+//  * Up to two units per CU (one round): a CU streams kCuBytesPerUs with one
+//    unit and is credited kPairBytesPerUs more with two (above the measured
+//    2-3e3: more streams also even out slow XCDs); a 32-key step of a unit
+//    alone on its CU takes kStepUs, a step of a second unit beside it kPairUs
+//    and kPairWaveUs for each of its live waves (32 rows).  (Attention of the 16-request 8B batch: 200
+//    units of up to 66 steps 45.5 us, 328 of up to 29 39.0, 512 of up to 15
+//    39.2; a rank of the 70B shape: 294 units 167 us, 512 115-117; long
+//    context: 256 units 209 us, 448 197, 512 195.)
+//    Units past the first kFreeStarts hold up each other's first blocks by
+//    kUnitStartUs each.  Short launches run at a higher clock (2.7 GHz against
+//    2.1-2.2 from ~100 us on), which prices the second unit's share down to
+//    kShortClock.
+//  * More units (several rounds): kUnitFixedUs per unit and kBlockUs per step,
+//    dealt longest first, and kChipBytesPerUs.  Head_dim 64 is always priced
+//    this way, streaming by the share of the slots that the units fill.
+constexpr double kCallUs = 6.0;
+constexpr double kUnitStartUs = 0.02;
+constexpr int kFreeStarts = 167;
+constexpr double kCombineUs = 3.0;
+constexpr double kCuBytesPerUs = 22.0e3;
+constexpr double kPairBytesPerUs = 7.2e3;
+constexpr double kCuMostBytesPerUs = 30.0e3;   // of one CU while others are done
+constexpr double kBytesPerStep = 32 * 512.0;    // K and V at head_dim 128
+constexpr double kTileReread = 0.3;   // HBM cost of a chunk's further row tiles (most hit L2)
+constexpr double kStepUs = 0.72;
+constexpr double kPairUs = 0.1;
+constexpr double kPairWaveUs = 0.03;
+constexpr double kShortClock = 0.78;
 constexpr double kChipBytesPerUs = 5.8e6;
 constexpr double kBlockUs = 1.0;
 constexpr double kUnitFixedUs = 6.0;
-constexpr double kCombineUs = 3.0;
 constexpr int kCUs = 256;
 constexpr int kSlots = 2 * kCUs;  // resident workgroups: two per CU
 
@@ -131,50 +155,99 @@ double lpt_makespan(std::vector<std::pair<double, int64_t>> &units) {
   return runs.back().first;
 }
 
+// A request's units: 32-key steps and live waves of each, the share of their
+// K/V bytes that other tiles do not stream, and their number.
+struct UnitRun {
+  int32_t steps, live;
+  double share;
+  int64_t count;
+};
+
+// Time the steps of `units` take: one round (at most kSlots units) by the
+// longest pair when unit i of the longest-first order shares a CU with unit
+// kCUs + i, several rounds by longest-first dealing.
+static double steps_us(std::vector<UnitRun> &units, int64_t total, int32_t head_dim) {
+  if (total > kSlots || head_dim == 64) {
+    std::vector<std::pair<double, int64_t>> timed;
+    timed.reserve(units.size());
+    for (const UnitRun &u : units) timed.push_back({kUnitFixedUs + u.steps * kBlockUs, u.count});
+    return lpt_makespan(timed);
+  }
+  std::stable_sort(units.begin(), units.end(), [](const UnitRun &x, const UnitRun &y) { return x.steps > y.steps; });
+  double worst = 0;
+  // walk unit i and its partner kCUs + i through the runs together
+  size_t p = 0;
+  int64_t p_left = 0, skip = kCUs;
+  for (; p < units.size(); ++p) {
+    if (skip < units[p].count) {
+      p_left = units[p].count - skip;
+      break;
+    }
+    skip -= units[p].count;
+  }
+  int64_t placed = 0;
+  for (size_t i = 0; i < units.size() && placed < kCUs; ++i) {
+    int64_t left = std::min<int64_t>(units[i].count, kCUs - placed);
+    placed += left;
+    while (left > 0) {
+      const bool pair = p < units.size();
+      const int64_t take = pair ? std::min(left, p_left) : left;
+      const double own = units[i].steps * units[i].share, other = pair ? units[p].steps * units[p].share : 0.0;
+      worst = std::max(worst, (own + other) * kBytesPerStep / kCuMostBytesPerUs);
+      const double alone = units[i].steps * kStepUs;
+      const double clock = kShortClock + (1.0 - kShortClock) * std::min(1.0, alone / 60.0);
+      worst = std::max(worst, alone + (pair ? units[p].steps * (kPairUs + units[p].live * kPairWaveUs) * clock : 0.0));
+      left -= take;
+      if (pair && (p_left -= take) == 0 && ++p < units.size()) p_left = units[p].count;
+    }
+  }
+  return worst + kUnitStartUs * std::max<int64_t>(0, total - kFreeStarts);
+}
+
 // Plan for one choice of per-request chunk lengths `ck` (prefix keys per
 // unit, whole 32-key blocks, at most kMaxChunk) with 128-row tiles.  The
-// cost estimate is the larger of the longest-first makespan of the units
-// and the chip-wide streaming time (K/V plus the split partials, at a rate
-// scaled by the share of workgroup slots the units fill), plus the combine
-// pass when a prefix is split.  evaluate_plan fills everything but
-// the makespan and returns the unit list; `bound` is a lower bound of the
-// estimate (the makespan replaced by max(longest unit, total / slots)).
+// estimate is kCallUs, the merge when a prefix is split, and the larger of
+// the steps' time and the streaming time (K/V plus the split partials).
+// evaluate_plan fills everything but the steps' time and returns the unit
+// list; `bound` is a lower bound of the estimate.
 static AttnPlan evaluate_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_host, int32_t hkv,
                        int32_t group, int32_t head_dim, int32_t rows_per_tile, const std::vector<int32_t> &ck,
-                       std::vector<std::pair<double, int64_t>> &units, double &fixed, double &bound) {
+                       std::vector<UnitRun> &units, double &fixed, double &bound) {
   AttnPlan p;
   p.rows_per_tile = rows_per_tile;
   p.chunk_len = ck;
   const double key_bytes = 4.0 * head_dim;  // bf16 K and V of one key of one kv-head
-  double kv_bytes = 0, partial_bytes = 0, total = 0;
+  double kv_bytes = 0, partial_bytes = 0;
+  int32_t longest = 0;
   units.clear();
   for (int32_t r = 0; r < B; ++r) {
     const int32_t n = indptr_host[r + 1] - indptr_host[r];
     const int32_t L = plen_host[r];
+    const int32_t rows = n * group;
     const int32_t tiles = row_tiles(n, group, rows_per_tile);
     const int32_t chunks = prefix_chunks(L, ck[r]);
-    const int64_t cnt = (int64_t)hkv * tiles * chunks;
-    p.units += cnt;
+    p.units += (int64_t)hkv * tiles * chunks;
     p.row_groups += (int64_t)hkv * tiles;
-    kv_bytes += (double)hkv * tiles * (L + n) * key_bytes;
+    kv_bytes += (double)hkv * (1.0 + kTileReread * (tiles - 1)) * (L + n) * key_bytes;
     if (chunks > 1) {
       p.needs_combine = true;
-      partial_bytes += hkv * chunks * n * group * (head_dim * 2.0 + 8.0);
+      partial_bytes += hkv * chunks * (double)rows * (head_dim * 2.0 + 8.0);
     }
-    // every chunk pays the fixed cost; the tree block is spread over them
-    const double blocks = ceil_div(std::min(L, ck[r]), 32) + (double)ceil_div(n, 32) / chunks;
-    units.push_back({kUnitFixedUs + blocks * kBlockUs, cnt});
-    total += units.back().first * cnt;
+    // the tree block is spread over the chunks
+    const int32_t steps = ceil_div(std::min(L, ck[r]), 32) + ceil_div(ceil_div(n, 32), chunks);
+    longest = std::max(longest, steps);
+    const int32_t full = rows / rows_per_tile, last = rows % rows_per_tile;
+    const double share = (1.0 + kTileReread * (tiles - 1)) / tiles;
+    if (full > 0) units.push_back({steps, rows_per_tile / 32, share, (int64_t)hkv * chunks * full});
+    if (last > 0) units.push_back({steps, ceil_div(last, 32), share, (int64_t)hkv * chunks});
   }
-  double longest = 0;
-  for (const auto &u : units) longest = std::max(longest, u.first);
-  // the chip streams at full rate only with every workgroup slot busy
-  const double occupancy = std::min(1.0, (double)p.units / kSlots);
-  const double stream = (kv_bytes + partial_bytes) / (kChipBytesPerUs * occupancy);
-  const double combine = p.needs_combine ? kCombineUs + partial_bytes / kChipBytesPerUs : 0.0;
-  fixed = combine;
-  p.est_us = std::max(stream, 0.0);  // completed with the makespan by make_plan
-  bound = std::max({stream, longest, total / kSlots}) + combine;
+  const double alone = (double)std::min<int64_t>(p.units, kCUs);
+  const double paired = (double)std::min<int64_t>(std::max<int64_t>(p.units - kCUs, 0), kCUs);
+  const double rate = head_dim == 64 || p.units > kSlots ? kChipBytesPerUs * (alone + paired) / kSlots
+                                                         : alone * kCuBytesPerUs + paired * kPairBytesPerUs;
+  fixed = kCallUs + (p.needs_combine ? kCombineUs + partial_bytes / rate : 0.0);
+  p.est_us = (kv_bytes + partial_bytes) / rate;  // completed with the steps' time by make_plan
+  bound = std::max(p.est_us, longest * kStepUs) + fixed;
   p.padded_grid = pad_to_xcds(p.units);
   if (p.needs_combine) {
     p.ws_o_bytes = round_up((size_t)p.units * kMaxRowsPerTile * head_dim * 2, 256);  // bf16
@@ -231,7 +304,7 @@ AttnPlan make_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_ho
     std::vector<int32_t> ck;
   };
   std::vector<Cand> cands;
-  std::vector<std::pair<double, int64_t>> units;
+  std::vector<UnitRun> units;
   double fixed, bound;
   auto add = [&](int32_t fm, int32_t c, std::vector<int32_t> ck) {
     for (const Cand &x : cands)
@@ -250,7 +323,7 @@ AttnPlan make_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_ho
     for (int32_t r = 0; r < B; ++r)
       work += (int64_t)hkv * row_tiles(indptr_host[r + 1] - indptr_host[r], group, rt) *
               std::max(1, ceil_div(plen_host[r], kKeysPerBlock));
-    for (int32_t target : {256, 320, 384, 448, 512, 576, 640, 768, 1024}) {
+    for (int32_t target : {160, 192, 224, 256, 288, 320, 352, 384, 416, 448, 512, 576, 640, 768, 1024}) {
       const int64_t per_unit = std::max<int64_t>(4, (work + target - 1) / target);
       for (int32_t r = 0; r < B; ++r) {
         const int32_t blocks = ceil_div(std::max(plen_host[r], 0), kKeysPerBlock);
@@ -265,21 +338,49 @@ AttnPlan make_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_ho
       add(0, 0, ck);
     }
   }
-  // candidates in the order they were generated break ties (larger chunks first)
+  // The cheapest estimate wins; at head_dim 128, among plans of more than a
+  // unit per CU within kTie of it (what the estimate is good for), the one of
+  // fewest units: it has less to merge, and in the one-call step the argmax
+  // rows find free slots from the start.  (Step of the 8B batch: 512 units
+  // 66.2 us, 464 64.2, 440 59.5, 416 58-59; its attention alone 36-39 for all.)
+  // A plan whose partials fit the static scratch is taken even at kScratchCost
+  // times the estimate, so that the allocation-free call can run the batch.
+  constexpr double kTie = 1.1, kScratchCost = 1.6;
   std::stable_sort(cands.begin(), cands.end(), [](const Cand &x, const Cand &y) { return x.bound < y.bound; });
-  bool have = false;
-  for (const Cand &cd : cands) {
-    if (have && cd.bound >= best.est_us * 0.98) break;
-    AttnPlan p = evaluate_plan(B, indptr_host, plen_host, hkv, group, head_dim, rt, cd.ck, units, fixed, bound);
-    p.est_us = std::max(p.est_us, lpt_makespan(units)) + fixed;
-    // the batch-wide fields rebuild the chunks when there is no plan table
-    p.chunk_target = cd.fm ? cd.c : kMaxChunk;
-    p.chunk_floor = cd.fm ? cd.fm : 32;
-    if (!have || p.est_us < best.est_us * 0.98) {
-      best = std::move(p);
-      have = true;
-    }
+  struct Priced {
+    size_t cand;
+    double est;
+    int64_t units;
+    bool fits;   // its partials fit the static scratch
+  };
+  std::vector<Priced> priced;
+  double least = 0, least_fit = 0;   // 0: none yet
+  for (size_t i = 0; i < cands.size(); ++i) {
+    if (least > 0 && cands[i].bound >= least * kScratchCost) break;
+    if (least_fit > 0 && cands[i].bound >= least_fit * kTie) break;
+    const AttnPlan p =
+        evaluate_plan(B, indptr_host, plen_host, hkv, group, head_dim, rt, cands[i].ck, units, fixed, bound);
+    const double est = std::max(p.est_us, steps_us(units, p.units, head_dim)) + fixed;
+    const bool fits = p.ws_bytes <= ADASERVE_TREE_ATTN_SCRATCH_BYTES;
+    priced.push_back({i, est, p.units, fits});
+    if (least == 0 || est < least) least = est;
+    if (fits && (least_fit == 0 || est < least_fit)) least_fit = est;
   }
+  const bool use_fit = least_fit > 0 && least_fit <= least * kScratchCost;
+  const Priced *pick = nullptr;
+  for (const Priced &x : priced)
+    if ((x.fits || !use_fit) && (!pick || x.est < pick->est)) pick = &x;
+  if (head_dim == 128 && pick->units > kCUs) {
+    const double tie = pick->est * kTie;
+    for (const Priced &x : priced)
+      if ((x.fits || !use_fit) && x.est <= tie && x.units > kCUs && x.units < pick->units) pick = &x;
+  }
+  const Cand &chosen = cands[pick->cand];
+  best = evaluate_plan(B, indptr_host, plen_host, hkv, group, head_dim, rt, chosen.ck, units, fixed, bound);
+  best.est_us = pick->est;
+  // the batch-wide fields rebuild the chunks when there is no plan table
+  best.chunk_target = chosen.fm ? chosen.c : kMaxChunk;
+  best.chunk_floor = chosen.fm ? chosen.fm : 32;
   best.single_tile = true;
   for (int32_t r = 0; r < B; ++r)
     best.single_tile &= row_tiles(indptr_host[r + 1] - indptr_host[r], group, rt) == 1;

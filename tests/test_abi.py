@@ -119,6 +119,20 @@ def _verify_noalloc(lib, ip, pl, hq=8, hkv=2, d=128, scale=0.1, bt_stride=None):
         pl.ctypes.data, hq, hkv, d, 16, scale, ada.ADASERVE_BF16, FAKE, None)
 
 
+@pytest.mark.parametrize("sizes,lens,hq,hkv", [
+    ([92], [190875], 32, 2),
+    ([85, 12, 40, 3], [158938, 9000, 64, 30000], 32, 2),
+    ([113, 20, 64, 7, 90], [38351, 12000, 8193, 300, 20000], 64, 8),
+    ([50, 9, 31, 22] * 6, [15498, 4000, 9000, 1200] * 6, 16, 2),
+])
+def test_plans_prefer_partials_that_fit_the_static_scratch(lib, sizes, lens, hq, hkv):
+    """Long prefixes that can be split into partials of at most the static
+    scratch are (finer splits would be estimated somewhat cheaper), so the
+    allocation-free call takes them."""
+    need = _ws(np.concatenate([[0], np.cumsum(sizes)]), lens, hq=hq, hkv=hkv)
+    assert 0 < need <= ada.TREE_ATTN_SCRATCH_BYTES
+
+
 def test_verify_noalloc_rejects_batches_past_the_scratch(lib):
     # a plan needing more split-KV partials than the static scratch holds is
     # refused before anything is enqueued, with the sizes in the message
