@@ -108,6 +108,21 @@ def test_commit_drawn_batches(torch_cuda, seed):
     _check(torch_cuda, b, alen, nodes)
 
 
+@pytest.mark.parametrize("hkv,rows", [(1, 1), (8, 7), (8, 8), (8, 9), (8, 17), (3, 128)])
+def test_commit_copy_batch_edges(torch_cuda, hkv, rows):
+    """Rows of 16 pieces (D = 128 bf16) around the 1024 pieces that a
+    workgroup copies at a time: less than one piece per thread, one row below
+    and above a batch, several batches with a remainder; with a request of
+    one row beside it."""
+    b = make_batch(parents=[chain_tree(rows), chain_tree(2)], prefix_lens=[21, 16], num_q_heads=hkv,
+                   num_kv_heads=hkv, head_dim=128, vocab=64, seed=rows, reserve_tokens=rows)
+    nodes = np.full((2, rows), -1, np.int32)
+    nodes[0] = np.arange(rows)
+    nodes[1, 0] = 0
+    new_len = _check(torch_cuda, b, np.array([rows, 1], np.int32), nodes)
+    assert new_len.tolist() == [21 + rows, 17]
+
+
 def alen_bound(parents):
     """Rows an accepted path can take: the deepest node's depth + 1."""
     out = []
