@@ -353,6 +353,7 @@ __device__ int draw_in_rounds(const char *prow, const char *qrow, int vocab, con
 // (R.mp, 1 / R.ip); inclusive prefix into sh.cum.  No pass over the row.
 __device__ void target_rounds(const Residual &R, const float4 *parts, int sub, int nrounds, Shared &sh) {
   const int t = threadIdx.x;
+  __syncthreads();  // a draw that found no mass leaves without a barrier after its reads of sh.cum
   if (t < 64) {
     float m = 0.f;
     if (t < nrounds * sub) {
