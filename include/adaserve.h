@@ -111,6 +111,11 @@ size_t adaserve_tree_attn_workspace_bytes(int32_t num_requests, const int32_t *n
  * prefix is split into chunks, each chunk's own normalised output is kept in
  * bf16 and the chunks are merged with fp32 weights.  F32 computes in fp32
  * throughout.
+ * F32: a key of weight 0, and every tree node off i's path, adds nothing to
+ * the output of i whatever its value row holds (an Inf or NaN in one branch
+ * stays in the nodes that see it).  BF16 multiplies the values of all of a
+ * request's nodes by their weights, 0 for the nodes off the path, so there
+ * tree and prefix values must be finite (0 * Inf is NaN).
  * Slots past L_r in the last page and pages not listed for r are never read
  * into the result (they may hold NaN).  Block-table entries outside
  * [0, num_pages) are treated as all-zero pages.  The device arrays must equal

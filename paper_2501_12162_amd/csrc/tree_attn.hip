@@ -938,21 +938,24 @@ __global__ __launch_bounds__(kWavesF32 * 64) void tree_attn_f32_kernel(TreeAttnA
 
   f32x4 o[RB][NH][4];
   float m[RB], l[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    m[rb] = -FLT_MAX;
-    l[rb] = 0.f;
-#pragma unroll
-    for (int h = 0; h < NH; ++h)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) o[rb][h][k] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
   int32_t page = -1;   // of the block in kr / vr
-  if (b0 < b1) {
-    page = page_of(b0);
-    load_k(b0, page);
-    load_v(b0, page);
-  }
+  auto start = [&]() {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      m[rb] = -FLT_MAX;
+      l[rb] = 0.f;
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[rb][h][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    if (b0 < b1) {
+      page = page_of(b0);
+      load_k(b0, page);
+      load_v(b0, page);
+    }
+  };
+  start();
   // The ancestor sets of the lane's rows' nodes, while the first block's loads
   // are in flight: bit i is 1 when node i is on the root-to-node path.  The
   // walk stops at anything that is not a parent strictly before its child.
@@ -975,132 +978,192 @@ __global__ __launch_bounds__(kWavesF32 * 64) void tree_attn_f32_kernel(TreeAttnA
     }
   }
 
-  // The next block's K and V replace this one's as soon as they are used
-  // (past the last block the last one is loaded again).
-  for (int b = b0; b < b1; ++b) {
-    const int bn = min(b + 1, b1 - 1);
-    const int32_t page_next = page_of(bn);
-    f32x4 s[RB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) s[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-          s[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[c][e], qf[rb][c][e], s[rb], 0, 0, 0);
-    load_k(bn, page_next);
-
-    // s[rb][e]: key 4 q + e of the block, row j
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s[rb][e] *= a.sm_scale;
-    const bool prefix = b < n_prefix_blocks;
-    const int tb = b - n_prefix_blocks;
-    const int valid = prefix ? min(kPageSize, L - b * kPageSize) : min(16, n - tb * 16);
-    const bool zero_page = prefix && page < 0;
-    if (!prefix || valid < 16 || zero_page) {
+  // The values of block b that are not finite, taken out of vr and added to the
+  // rows that weigh them.
+  auto add_not_finite = [&](const f32x4 (&s)[RB], int b) {
+    int64_t stride;
+    int rows;
+    const float *vb = rows_at(a.v_pages, a.v_tree, b, page, stride, rows);
+    if (page < 0 && b < n_prefix_blocks) rows = 0;   // a zero page
+#pragma unroll 1
+    for (int key = 0; key < rows; ++key) {
+      const float *vp = vb + key * stride + q * 16;
+      float p[RB];
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
-        uint32_t seen = 0xffffu;
-        if (!prefix) {
-          const uint32_t w0 = an[rb][0], w1 = an[rb][1], w2 = an[rb][2], w3 = an[rb][3];
-          const uint32_t w = (tb & 4) ? ((tb & 2) ? w3 : w2) : ((tb & 2) ? w1 : w0);
-          seen = (tb & 1) ? w >> 16 : w;
+        const float p01 = (key & 1) ? s[rb][1] : s[rb][0], p23 = (key & 1) ? s[rb][3] : s[rb][2];
+        p[rb] = __shfl((key & 2) ? p23 : p01, (key >> 2) * 16 + j, 64);
+      }
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const f32x4 v = *(const f32x4 *)(vp + h * 64 + i * 4);   // o[.][h][k][i] is column 64 h + 16 q + 4 i + k
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+              if (p[rb] != 0.f && !(fabsf(v[k]) < INFINITY)) o[rb][h][k][i] = fmaf(p[rb], v[k], o[rb][h][k][i]);
+          __builtin_amdgcn_sched_barrier(0);   // one load's values at a time: no registers are left for more
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int key = q * 4 + e;
-          const float x = zero_page ? 0.f : s[rb][e];
-          s[rb][e] = key < valid && ((seen >> key) & 1u) ? x : -INFINITY;
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int h = 0; h < NH; ++h)
-          if (zero_page || q * 4 + e >= valid) vr[e][h] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    float mn[RB];
-    bool up = false;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const float bm = max_over_lane_rows(__builtin_elementwise_maximum(__builtin_elementwise_maximum(s[rb][0], s[rb][1]),
-                                                                        __builtin_elementwise_maximum(s[rb][2], s[rb][3])));
-      mn[rb] = bm > m[rb] ? bm : m[rb];
-      up |= bm > m[rb];
-    }
-    if (__any(up)) {
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const float al = expf(m[rb] - mn[rb]);
-        m[rb] = mn[rb];
-        l[rb] *= al;
-#pragma unroll
-        for (int h = 0; h < NH; ++h)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) o[rb][h][i] *= al;
-      }
-    }
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        s[rb][e] = expf(s[rb][e] - m[rb]);
-        l[rb] += s[rb][e];
-      }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
       for (int h = 0; h < NH; ++h)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i) vr[e][h][i] = fabsf(vr[e][h][i]) < INFINITY ? vr[e][h][i] : 0.f;
+  };
+  // The next block's K and V replace this one's as soon as they are used
+  // (past the last block the last one is loaded again).
+  auto blocks = [&](auto careful) {
+    constexpr bool kCareful = decltype(careful)::value;
+    for (int b = b0; b < b1; ++b) {
+      const int bn = min(b + 1, b1 - 1);
+      const int32_t page_next = page_of(bn);
+      f32x4 s[RB];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) s[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
           for (int rb = 0; rb < RB; ++rb)
-            o[rb][h][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[e][h][i], s[rb][e], o[rb][h][i], 0, 0, 0);
-    load_v(bn, page_next);
-    page = page_next;
-  }
+            s[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[c][e], qf[rb][c][e], s[rb], 0, 0, 0);
+      load_k(bn, page_next);
 
-  // The waves' (max, sum, output) to LDS, then the merge.
+      // s[rb][e]: key 4 q + e of the block, row j
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int rl = rb * 16 + j;
-    const float ls = sum_over_lane_rows(l[rb]);
-    if (q == 0) {
-      mw[wave][rl] = m[rb];
-      lw[wave][rl] = ls;
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[rb][e] *= a.sm_scale;
+      const bool prefix = b < n_prefix_blocks;
+      const int tb = b - n_prefix_blocks;
+      const int valid = prefix ? min(kPageSize, L - b * kPageSize) : min(16, n - tb * 16);
+      const bool zero_page = prefix && page < 0;
+      if (!prefix || valid < 16 || zero_page) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          uint32_t seen = 0xffffu;
+          if (!prefix) {
+            const uint32_t w0 = an[rb][0], w1 = an[rb][1], w2 = an[rb][2], w3 = an[rb][3];
+            const uint32_t w = (tb & 4) ? ((tb & 2) ? w3 : w2) : ((tb & 2) ? w1 : w0);
+            seen = (tb & 1) ? w >> 16 : w;
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int key = q * 4 + e;
+            const float x = zero_page ? 0.f : s[rb][e];
+            s[rb][e] = key < valid && ((seen >> key) & 1u) ? x : -INFINITY;
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int h = 0; h < NH; ++h)
+            if (zero_page || q * 4 + e >= valid) vr[e][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      float mn[RB];
+      bool up = false;
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        const float bm = max_over_lane_rows(__builtin_elementwise_maximum(__builtin_elementwise_maximum(s[rb][0], s[rb][1]),
+                                                                          __builtin_elementwise_maximum(s[rb][2], s[rb][3])));
+        mn[rb] = bm > m[rb] ? bm : m[rb];
+        up |= bm > m[rb];
+      }
+      if (__any(up)) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          const float al = expf(m[rb] - mn[rb]);
+          m[rb] = mn[rb];
+          l[rb] *= al;
+#pragma unroll
+          for (int h = 0; h < NH; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[rb][h][i] *= al;
+        }
+      }
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s[rb][e] = expf(s[rb][e] - m[rb]);
+          l[rb] += s[rb][e];
+        }
+      if constexpr (kCareful) add_not_finite(s, b);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+              o[rb][h][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[e][h][i], s[rb][e], o[rb][h][i], 0, 0, 0);
+      load_v(bn, page_next);
+      page = page_next;
     }
-    float *dst = mo + (wave * RT + rl) * LDO;
+  };
+  // The waves' (max, sum, output) to LDS, then the merge; true when a value of
+  // this thread's is NaN.
+  auto merge = [&]() -> bool {
 #pragma unroll
-    for (int h = 0; h < NH; ++h)
+    for (int rb = 0; rb < RB; ++rb) {
+      const int rl = rb * 16 + j;
+      const float ls = sum_over_lane_rows(l[rb]);
+      if (q == 0) {
+        mw[wave][rl] = m[rb];
+        lw[wave][rl] = ls;
+      }
+      float *dst = mo + (wave * RT + rl) * LDO;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        *(f32x4 *)(dst + h * 64 + q * 16 + i * 4) =
-            f32x4{o[rb][h][0][i], o[rb][h][1][i], o[rb][h][2][i], o[rb][h][3][i]};
-  }
-  __syncthreads();
-  for (int it = tid; it < RT * (D / 4); it += kT) {
-    const int rl = it / (D / 4), col = it % (D / 4) * 4;
-    const int row = row0 + rl;
-    if (row >= M) continue;
-    float mm = mw[0][rl];
+      for (int h = 0; h < NH; ++h)
 #pragma unroll
-    for (int w = 1; w < NW; ++w) mm = fmaxf(mm, mw[w][rl]);
-    float den = 0.f;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const float wt = expf(mw[w][rl] - mm);
-      den += wt * lw[w][rl];
-      acc += *(const f32x4 *)(mo + (w * RT + rl) * LDO + col) * wt;
+        for (int i = 0; i < 4; ++i)
+          *(f32x4 *)(dst + h * 64 + q * 16 + i * 4) =
+              f32x4{o[rb][h][0][i], o[rb][h][1][i], o[rb][h][2][i], o[rb][h][3][i]};
     }
-    const int node = row / G, hh = row - node * G;
-    f32x4 res = {0.f, 0.f, 0.f, 0.f};
-    if (den > 0.f) res = acc / den;
-    *(f32x4 *)((float *)a.out + ((int64_t)(node_base + node) * a.num_q_heads + g * G + hh) * D + col) = res;
+    __syncthreads();
+    bool nan = false;
+    for (int it = tid; it < RT * (D / 4); it += kT) {
+      const int rl = it / (D / 4), col = it % (D / 4) * 4;
+      const int row = row0 + rl;
+      if (row >= M) continue;
+      float mm = mw[0][rl];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) mm = fmaxf(mm, mw[w][rl]);
+      float den = 0.f;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float wt = expf(mw[w][rl] - mm);
+        den += wt * lw[w][rl];
+        acc += *(const f32x4 *)(mo + (w * RT + rl) * LDO + col) * wt;
+      }
+      const int node = row / G, hh = row - node * G;
+      f32x4 res = {0.f, 0.f, 0.f, 0.f};
+      if (den > 0.f) res = acc / den;
+      nan |= res[0] != res[0] || res[1] != res[1] || res[2] != res[2] || res[3] != res[3];
+      *(f32x4 *)((float *)a.out + ((int64_t)(node_base + node) * a.num_q_heads + g * G + hh) * D + col) = res;
+    }
+    return nan;
+  };
+  // A key of weight 0 (a node off the row's path above all) adds nothing,
+  // whatever its V, but 0 * Inf is NaN on the matrix cores.  So a workgroup
+  // that merged a NaN goes over its keys again with the values that are not
+  // finite kept out of the products, and writes its rows a second time.
+  // (Testing every block's V as it is used instead cost 10% at D = 128, 40.0 ->
+  // 43.9 us for the 4 requests above; every wave's output before the merge 2%.)
+  blocks(std::false_type{});
+  const bool nan = merge();
+  if (__builtin_expect(__syncthreads_or(nan), 0)) {
+    page_base = b0;
+    load_pages();
+    start();
+    blocks(std::true_type{});
+    merge();
   }
 }
 

@@ -191,6 +191,53 @@ def test_f32_row_and_key_remainders(torch_cuda, head_dim, hq, hkv, repeat):
     assert float(np.abs(out - ref).max()) <= 2e-5
 
 
+@pytest.mark.parametrize("head_dim,hq,hkv,repeat", [(64, 2, 2, 1), (128, 8, 2, 1), (64, 22, 2, 12), (128, 16, 4, 15)])
+def test_f32_values_that_are_not_finite_stay_on_their_paths(torch_cuda, head_dim, hq, hkv, repeat):
+    """A node whose V holds Inf or NaN, and one whose K does, change the output
+    of the nodes that see them and, bit for bit, of no other (16- and 32-row
+    tiles); of the former, only the columns that hold them change when it is
+    the V.  A prefix key of weight 0 (its score 1000 below) adds nothing
+    either, whatever its V."""
+    sizes = [40, 1, 128, 17, 33] * repeat
+    lens = [70, 130, 0, 300, 16] * repeat
+    rng = np.random.Generator(np.random.PCG64(hq * head_dim))
+    parents = [random_tree(rng, n, 6) for n in sizes]
+    b = make_batch(parents=parents, prefix_lens=lens, num_q_heads=hq, num_kv_heads=hkv, head_dim=head_dim,
+                   dtype="f32", vocab=64, seed=hkv)
+    G = hq // hkv
+    r, t = 1, 77                               # the request of one node: a prefix key far below the others
+    node, page = int(b.node_indptr[r]), int(b.block_table[r, t // 16])
+    for g in range(hkv):
+        q = b.q[node, g * G:(g + 1) * G].astype(np.float64)
+        b.k_pages[page, g, t % 16] = np.linalg.pinv(q) @ np.full(G, -1000.0 / b.sm_scale)
+    d, (clean, *_) = run_device(b)
+    assert np.isfinite(clean).all()
+    assert float(np.abs(clean - oracle.tree_attn_batch(b)).max()) <= 2e-5   # the bound of the test above
+    b.v_pages[page, :, t % 16, ::3] = np.inf
+    sees_v, sees_k = np.zeros(b.total_nodes, bool), np.zeros(b.total_nodes, bool)
+    cols = np.array([0, 5, 18, head_dim - 1])
+    for r, n in enumerate(sizes):
+        if n == 1:
+            continue
+        a, par = int(b.node_indptr[r]), np.asarray(parents[r])
+        bad_v, bad_k = int(rng.integers(1, n)), int(rng.integers(1, n))
+        b.v_tree[a + bad_v][:, cols] = [np.inf, -np.inf, np.nan, np.inf]
+        b.k_tree[a + bad_k, :, 3] = np.nan if r % 2 else np.inf
+        for i in range(n):
+            path, v = [], i
+            while v >= 0:
+                path.append(v)
+                v = int(par[v])
+            sees_v[a + i], sees_k[a + i] = bad_v in path, bad_k in path
+    assert sees_v.any() and sees_k.any() and not (sees_v | sees_k).all()
+    _, (out, *_) = run_device(b)
+    np.testing.assert_array_equal(out[~sees_v & ~sees_k], clean[~sees_v & ~sees_k])
+    only_v = sees_v & ~sees_k
+    assert not np.isfinite(out[only_v][:, :, cols]).any()
+    rest = np.setdiff1d(np.arange(head_dim), cols)
+    np.testing.assert_array_equal(out[only_v][:, :, rest], clean[only_v][:, :, rest])
+
+
 def test_out_of_pool_pages_read_as_zero_pages(torch_cuda):
     """Block-table entries outside [0, num_pages) -- negative or past the pool
     -- act as all-zero pages: the call equals, bit for bit, the same batch
