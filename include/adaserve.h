@@ -14,7 +14,7 @@
  *   adaserve_node_argmax       the target's greedy choice at every node;
  *   adaserve_tree_accept       the longest accepted root path per request and
  *                              the tokens it commits;
- *   adaserve_tree_verify_step  the three above as one call (two launches);
+ *   adaserve_tree_verify_step  the three above as one call;
  *   adaserve_tree_accept_sampled  the same for sampled decoding (speculative
  *                              sampling over the tree);
  *   adaserve_commit_accepted_kv  the accepted path's keys and values written
@@ -233,7 +233,8 @@ int32_t adaserve_tree_accept(int32_t num_requests, int32_t total_nodes,
  * attention instead of after it); then the split-KV merge (when a prefix is
  * split) together with one acceptance wave per request.  F32 runs in two
  * launches too (its prefixes are never split: the second is the acceptance
- * alone).  Calls that share a workspace must not overlap in time.
+ * alone), or three when many short logits rows run faster in a launch of
+ * their own.  Calls that share a workspace must not overlap in time.
  */
 int32_t adaserve_tree_verify_step(int32_t num_requests, const int32_t *node_indptr,
                                   const int32_t *node_indptr_host, const int32_t *parent,

@@ -58,8 +58,9 @@ struct TreeAttnArgs {
 };
 
 hipError_t launch_tree_attn_bf16(TreeAttnArgs &a, int head_dim, bool needs_combine, hipStream_t stream);
-// The verification step in two launches: attention + argmax workgroups, then
-// the split-KV merge (when a prefix is split) + acceptance waves.
+// The verification step: attention + argmax workgroups (many short F32 rows
+// in a launch of their own), then the split-KV merge (when a prefix is split) +
+// acceptance waves.
 hipError_t launch_verify_step(TreeAttnArgs &a, int head_dim, bool bf16, bool needs_combine, hipStream_t stream);
 // Device address of the static split-KV scratch array on the current device
 // (ADASERVE_TREE_ATTN_SCRATCH_BYTES bytes, 256-byte aligned); looked up once

@@ -1262,11 +1262,22 @@ hipError_t launch_tree_attn_f32(const TreeAttnArgs &a, int head_dim, int64_t blo
   return hipGetLastError();
 }
 
+// An F32 argmax workgroup in the attention's grid takes the LDS and registers
+// of an F32 attention workgroup, so a CU holds one: many short rows wait for
+// their turn, and go into a launch of their own (full step, beside | apart:
+// 16 / 4 heads, D = 128, 32-node trees over 400 keys, vocabulary 4096: 256 rows
+// 27.0 | 30.0 us, 512 41.8 | 40.8, 1024 75.7 | 70.7, 4096 282 | 252; 4 / 4
+// heads 512 rows 24.2 | 28.8, 1024 34.2 | 30.8, 4096 112 | 81).  Long rows stream
+// as fast either way (65536 columns: 1024 rows 107 | 109, 2048 201 | 204;
+// 16384: 1024 78.1 | 77.7, 4096 292 | 282).
+constexpr int kF32RowsBeside = 768, kF32LongRow = 32768;
+
 hipError_t launch_verify_step(TreeAttnArgs &a, int head_dim, bool bf16, bool needs_combine, hipStream_t stream) {
   hipError_t e = zero16_address(&a.zero16);
   if (e != hipSuccess) return e;
   const dim3 block(kThreads);
-  const int64_t g1 = (a.units > 0 ? a.padded_grid : 0) + a.argmax_rows;
+  const bool apart = !bf16 && a.argmax_rows > kF32RowsBeside && a.vocab <= kF32LongRow;
+  const int64_t g1 = (a.units > 0 ? a.padded_grid : 0) + (apart ? 0 : a.argmax_rows);
   if (a.units == 0) a.padded_grid = 0;
   if (g1 > 0) {
     if (bf16) {
@@ -1275,6 +1286,10 @@ hipError_t launch_verify_step(TreeAttnArgs &a, int head_dim, bool bf16, bool nee
     } else {
       e = launch_tree_attn_f32(a, head_dim, g1, stream);
     }
+    if (e != hipSuccess) return e;
+  }
+  if (apart) {
+    e = launch_node_argmax(a.logits, a.logit_stride, a.argmax_rows, a.vocab, bf16, a.argmax_out, stream);
     if (e != hipSuccess) return e;
   }
   if (!needs_combine) a.merge_blocks = 0;

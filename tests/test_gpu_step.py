@@ -60,6 +60,23 @@ def test_step_on_ragged_batches(dtype, head_dim, hq, hkv):
         assert d.workspace_bytes > 0
 
 
+@pytest.mark.parametrize("head_dim,hq,hkv,requests,apart", [(128, 32, 8, 12, False), (64, 32, 8, 12, False),
+                                                            (128, 16, 4, 30, True), (64, 8, 4, 180, True)])
+def test_f32_step_on_32_row_tiles(head_dim, hq, hkv, requests, apart):
+    """F32 batches of at least 256 units of 32 rows (the plan's rule for the
+    32-row tiles), their argmax rows in the attention's launch and, for more
+    than 768 rows, in one of their own; with a plan table and past it (more
+    than 160 requests); the vocabulary ends part way through a workgroup's
+    last loads."""
+    rng = np.random.Generator(np.random.PCG64(331 + requests))
+    sizes = [int(x) for x in rng.integers(1, 70, size=requests)]
+    assert sum(-(-n * (hq // hkv) // 32) for n in sizes) * hkv >= 256
+    assert (sum(sizes) > 768) == apart
+    b = make_batch(parents=[random_tree(rng, n) for n in sizes], prefix_lens=[int(x) for x in rng.integers(0, 90, size=requests)],
+                   num_q_heads=hq, num_kv_heads=hkv, head_dim=head_dim, dtype="f32", vocab=4099, seed=requests, row_pad=3)
+    fused_matches_separate(b, check_oracle=True)
+
+
 def test_step_without_splits_and_with_a_depth_limit():
     """Short prefixes (no split-KV merge: the second launch is acceptance
     only) and max_accept below some trees' depth (those requests get -1)."""
