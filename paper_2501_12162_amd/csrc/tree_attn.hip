@@ -1018,6 +1018,10 @@ __global__ __launch_bounds__(kWavesF32 * 64) void tree_attn_f32_kernel(TreeAttnA
   // (past the last block the last one is loaded again).
   auto blocks = [&](auto careful) {
     constexpr bool kCareful = decltype(careful)::value;
+    // Puts the loop's matrix instructions where they start in the first half of
+    // a 32-byte line: in the second half the loop is 2.5% slower (the 4 requests
+    // above 39.1 | 40.1 us, 2 of 64 nodes over 2000 keys 55.7 | 57.4).
+    if constexpr (!kCareful) asm volatile(".p2align 6\ns_nop 0\ns_nop 0\ns_nop 0\ns_nop 0");
     for (int b = b0; b < b1; ++b) {
       const int bn = min(b + 1, b1 - 1);
       const int32_t page_next = page_of(bn);
@@ -1106,64 +1110,69 @@ __global__ __launch_bounds__(kWavesF32 * 64) void tree_attn_f32_kernel(TreeAttnA
       page = page_next;
     }
   };
-  // The waves' (max, sum, output) to LDS, then the merge; true when a value of
-  // this thread's is NaN.
-  auto merge = [&]() -> bool {
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const int rl = rb * 16 + j;
-      const float ls = sum_over_lane_rows(l[rb]);
-      if (q == 0) {
-        mw[wave][rl] = m[rb];
-        lw[wave][rl] = ls;
-      }
-      float *dst = mo + (wave * RT + rl) * LDO;
-#pragma unroll
-      for (int h = 0; h < NH; ++h)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          *(f32x4 *)(dst + h * 64 + q * 16 + i * 4) =
-              f32x4{o[rb][h][0][i], o[rb][h][1][i], o[rb][h][2][i], o[rb][h][3][i]};
-    }
-    __syncthreads();
-    bool nan = false;
-    for (int it = tid; it < RT * (D / 4); it += kT) {
-      const int rl = it / (D / 4), col = it % (D / 4) * 4;
-      const int row = row0 + rl;
-      if (row >= M) continue;
-      float mm = mw[0][rl];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) mm = fmaxf(mm, mw[w][rl]);
-      float den = 0.f;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const float wt = expf(mw[w][rl] - mm);
-        den += wt * lw[w][rl];
-        acc += *(const f32x4 *)(mo + (w * RT + rl) * LDO + col) * wt;
-      }
-      const int node = row / G, hh = row - node * G;
-      f32x4 res = {0.f, 0.f, 0.f, 0.f};
-      if (den > 0.f) res = acc / den;
-      nan |= res[0] != res[0] || res[1] != res[1] || res[2] != res[2] || res[3] != res[3];
-      *(f32x4 *)((float *)a.out + ((int64_t)(node_base + node) * a.num_q_heads + g * G + hh) * D + col) = res;
-    }
-    return nan;
-  };
-  // A key of weight 0 (a node off the row's path above all) adds nothing,
-  // whatever its V, but 0 * Inf is NaN on the matrix cores.  So a workgroup
-  // that merged a NaN goes over its keys again with the values that are not
-  // finite kept out of the products, and writes its rows a second time.
-  // (Testing every block's V as it is used instead cost 10% at D = 128, 40.0 ->
-  // 43.9 us for the 4 requests above; every wave's output before the merge 2%.)
   blocks(std::false_type{});
-  const bool nan = merge();
-  if (__builtin_expect(__syncthreads_or(nan), 0)) {
+  // A key of weight 0 (a node off the row's path above all) adds nothing,
+  // whatever its V, but 0 * Inf is NaN on the matrix cores.  A wave whose output
+  // holds a NaN goes over its keys again with the values that are not finite
+  // kept out of the products.  (Testing every block's V as it is used instead
+  // cost 10% at D = 128, 40.0 -> 43.9 us for the 4 requests above; testing the
+  // merged rows, which takes a barrier more, 9% for many short units, 128
+  // requests of 16 nodes over 100 keys, 8 / 8 heads, D = 64: 34.1 -> 37.3.)
+  float nan[2] = {0.f, 0.f};   // maxima, which a NaN passes through
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          nan[i] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(nan[i], o[rb][h][k][i]), o[rb][h][k][i + 2]);
+  nan[0] = __builtin_elementwise_maximum(nan[0], nan[1]);
+  if (__builtin_expect(__any(nan[0] != nan[0]), 0)) {
     page_base = b0;
     load_pages();
     start();
     blocks(std::true_type{});
-    merge();
+  }
+
+  // The waves' (max, sum, output) to LDS, then the merge.
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int rl = rb * 16 + j;
+    const float ls = sum_over_lane_rows(l[rb]);
+    if (q == 0) {
+      mw[wave][rl] = m[rb];
+      lw[wave][rl] = ls;
+    }
+    float *dst = mo + (wave * RT + rl) * LDO;
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *(f32x4 *)(dst + h * 64 + q * 16 + i * 4) =
+            f32x4{o[rb][h][0][i], o[rb][h][1][i], o[rb][h][2][i], o[rb][h][3][i]};
+  }
+  __syncthreads();
+  for (int it = tid; it < RT * (D / 4); it += kT) {
+    const int rl = it / (D / 4), col = it % (D / 4) * 4;
+    const int row = row0 + rl;
+    if (row >= M) continue;
+    float mm = mw[0][rl];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mm = fmaxf(mm, mw[w][rl]);
+    float den = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float wt = expf(mw[w][rl] - mm);
+      den += wt * lw[w][rl];
+      acc += *(const f32x4 *)(mo + (w * RT + rl) * LDO + col) * wt;
+    }
+    const int node = row / G, hh = row - node * G;
+    f32x4 res = {0.f, 0.f, 0.f, 0.f};
+    if (den > 0.f) res = acc / den;
+    *(f32x4 *)((float *)a.out + ((int64_t)(node_base + node) * a.num_q_heads + g * G + hh) * D + col) = res;
   }
 }
 
