@@ -110,7 +110,10 @@ constexpr int kSlots = 2 * kCUs;  // resident workgroups: two per CU
 // equal load, so the cost grows with the number of distinct durations, not
 // with the number of units.  `units` holds (duration, count) pairs in any
 // order; it is sorted in place.
-double lpt_makespan(std::vector<std::pair<double, int64_t>> &units) {
+using Durations = std::vector<std::pair<double, int64_t>>;
+static double deal_longest_first(const Durations &units, Durations &runs, double limit);
+
+double lpt_makespan(Durations &units) {
   std::sort(units.begin(), units.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
   size_t m = 0;  // merge equal durations
   for (size_t i = 0; i < units.size(); ++i) {
@@ -120,14 +123,24 @@ double lpt_makespan(std::vector<std::pair<double, int64_t>> &units) {
       units[m++] = units[i];
   }
   units.resize(m);
-  std::vector<std::pair<double, int64_t>> runs{{0.0, (int64_t)kSlots}};  // (load, slots), ascending
-  auto insert = [&runs](double load, int64_t slots) {
-    auto it = std::lower_bound(runs.begin(), runs.end(), load,
-                               [](const std::pair<double, int64_t> &x, double v) { return x.first < v; });
-    if (it != runs.end() && it->first == load)
-      it->second += slots;
+  Durations runs;
+  return deal_longest_first(units, runs, HUGE_VAL);
+}
+
+// The same for distinct durations in descending order; a makespan past `limit`
+// may be returned short, but still past it.  `runs` is scratch.
+static double deal_longest_first(const Durations &units, Durations &runs, double limit) {
+  runs.clear();
+  runs.push_back({0.0, (int64_t)kSlots});  // (load, slots), ascending from runs[head]
+  size_t head = 0;
+  auto insert = [&](double load, int64_t slots) {
+    // most new loads are among the highest
+    size_t i = runs.size();
+    while (i > head && runs[i - 1].first > load) --i;
+    if (i > head && runs[i - 1].first == load)
+      runs[i - 1].second += slots;
     else
-      runs.insert(it, {load, slots});
+      runs.insert(runs.begin() + i, {load, slots});
   };
   for (const auto &u : units) {
     const double t = u.first;
@@ -137,43 +150,45 @@ double lpt_makespan(std::vector<std::pair<double, int64_t>> &units) {
     // pass the next run's load (or the units run out): whole rounds move the
     // run up together; a last partial round splits it.
     while (c > 0) {
-      const double x0 = runs.front().first;
-      const int64_t k0 = runs.front().second;
+      const double x0 = runs[head].first;
+      const int64_t k0 = runs[head].second;
       if (c < k0) {
-        runs.front().second -= c;
+        runs[head].second -= c;
         insert(x0 + t, c);
         break;
       }
-      runs.erase(runs.begin());
-      int64_t rounds = c / k0;
-      if (!runs.empty())
-        rounds = std::min<int64_t>(rounds, std::max<int64_t>(1, (int64_t)std::ceil((runs.front().first - x0) / t)));
+      ++head;
+      int64_t rounds = 1;
+      if (c >= 2 * k0) {
+        rounds = c / k0;
+        if (head < runs.size())
+          rounds = std::min<int64_t>(rounds, std::max<int64_t>(1, (int64_t)std::ceil((runs[head].first - x0) / t)));
+      }
       c -= rounds * k0;
       insert(x0 + (double)rounds * t, k0);
     }
+    if (runs.back().first > limit) break;
   }
   return runs.back().first;
 }
 
-// A request's units: 32-key steps and live waves of each, the share of their
-// K/V bytes that other tiles do not stream, and their number.
-struct UnitRun {
-  int32_t steps, live;
-  double share;
-  int64_t count;
+// Buffers that the pricing of a batch's choices shares.
+struct PricingScratch {
+  std::vector<UnitRun> units;   // longest first
+  std::vector<int32_t> steps, chunks;
+  Durations timed, runs;
 };
 
-// Time the steps of `units` take: one round (at most kSlots units) by the
-// longest pair when unit i of the longest-first order shares a CU with unit
-// kCUs + i, several rounds by longest-first dealing.
-static double steps_us(std::vector<UnitRun> &units, int64_t total, int32_t head_dim) {
-  if (total > kSlots || head_dim == 64) {
-    std::vector<std::pair<double, int64_t>> timed;
-    timed.reserve(units.size());
-    for (const UnitRun &u : units) timed.push_back({kUnitFixedUs + u.steps * kBlockUs, u.count});
-    return lpt_makespan(timed);
-  }
-  std::stable_sort(units.begin(), units.end(), [](const UnitRun &x, const UnitRun &y) { return x.steps > y.steps; });
+// The time of one CU's units: `first` alone, or with `second` beside it.
+double pair_us(const UnitRun &first, const UnitRun *second) {
+  const double own = first.steps * first.share, other = second ? second->steps * second->share : 0.0;
+  const double alone = first.steps * kStepUs;
+  const double clock = kShortClock + (1.0 - kShortClock) * std::min(1.0, alone / 60.0);
+  return std::max((own + other) * kBytesPerStep / kCuMostBytesPerUs,
+                  alone + (second ? second->steps * (kPairUs + second->live * kPairWaveUs) * clock : 0.0));
+}
+
+double one_round_us(const std::vector<UnitRun> &units, int64_t total) {
   double worst = 0;
   // walk unit i and its partner kCUs + i through the runs together
   size_t p = 0;
@@ -192,11 +207,7 @@ static double steps_us(std::vector<UnitRun> &units, int64_t total, int32_t head_
     while (left > 0) {
       const bool pair = p < units.size();
       const int64_t take = pair ? std::min(left, p_left) : left;
-      const double own = units[i].steps * units[i].share, other = pair ? units[p].steps * units[p].share : 0.0;
-      worst = std::max(worst, (own + other) * kBytesPerStep / kCuMostBytesPerUs);
-      const double alone = units[i].steps * kStepUs;
-      const double clock = kShortClock + (1.0 - kShortClock) * std::min(1.0, alone / 60.0);
-      worst = std::max(worst, alone + (pair ? units[p].steps * (kPairUs + units[p].live * kPairWaveUs) * clock : 0.0));
+      worst = std::max(worst, pair_us(units[i], pair ? &units[p] : nullptr));
       left -= take;
       if (pair && (p_left -= take) == 0 && ++p < units.size()) p_left = units[p].count;
     }
@@ -204,57 +215,179 @@ static double steps_us(std::vector<UnitRun> &units, int64_t total, int32_t head_
   return worst + kUnitStartUs * std::max<int64_t>(0, total - kFreeStarts);
 }
 
-// Plan for one choice of per-request chunk lengths `ck` (prefix keys per
-// unit, whole 32-key blocks, at most kMaxChunk) with 128-row tiles.  The
-// estimate is kCallUs, the merge when a prefix is split, and the larger of
-// the steps' time and the streaming time (K/V plus the split partials).
-// evaluate_plan fills everything but the steps' time and returns the unit
-// list; `bound` is a lower bound of the estimate.
-static AttnPlan evaluate_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_host, int32_t hkv,
-                       int32_t group, int32_t head_dim, int32_t rows_per_tile, const std::vector<int32_t> &ck,
-                       std::vector<UnitRun> &units, double &fixed, double &bound) {
-  AttnPlan p;
-  p.rows_per_tile = rows_per_tile;
-  p.chunk_len = ck;
+// Time the steps of `w.units` take: one round (at most kSlots units) by
+// one_round_us, several rounds by longest-first dealing (a time past `limit`
+// may be returned short, but still past it).
+static double steps_us(PricingScratch &w, int64_t total, int32_t head_dim, double limit) {
+  if (total <= kSlots && head_dim != 64) return one_round_us(w.units, total);
+  w.timed.clear();
+  for (const UnitRun &u : w.units) {
+    const double t = kUnitFixedUs + u.steps * kBlockUs;
+    if (!w.timed.empty() && w.timed.back().first == t)
+      w.timed.back().second += u.count;
+    else
+      w.timed.push_back({t, u.count});
+  }
+  return deal_longest_first(w.timed, w.runs, limit);
+}
+
+// Workspace of a plan that splits a prefix: per unit, kMaxRowsPerTile bf16 output
+// rows, then fp32 (max, denominator) pairs.
+static size_t partial_rows_bytes(int64_t units, int32_t head_dim) {
+  return round_up((size_t)units * kMaxRowsPerTile * head_dim * 2, 256);
+}
+static size_t partial_bytes(int64_t units, int32_t head_dim) {
+  return partial_rows_bytes(units, head_dim) + round_up((size_t)units * kMaxRowsPerTile * 2 * sizeof(float), 256);
+}
+
+// ceil(a / b) by a float division, several times as fast as an integer one:
+// exact while a + b < 2^22 (block counts are at most 2^18), where the quotient
+// stays at least 0.5 / b off the integers and rounds by less.
+static inline int32_t quick_ceil_div(int32_t a, int32_t b) {
+  return (int32_t)(((float)(a + b) - 0.5f) / (float)b);
+}
+
+// Blocks of the tree in a chunk's steps: the at most 4 tree blocks are spread
+// over the chunks.
+static inline int32_t tree_steps(int32_t tree_blocks, int32_t chunks) {
+  return 1 + (tree_blocks > chunks) + (tree_blocks > 2 * chunks) + (tree_blocks > 3 * chunks);
+}
+
+// What the plan choices of a batch share: the sizes of each request, in the
+// bf16 kernel's units.
+struct PlanRequest {
+  int32_t blocks, tree_blocks;   // of 32 keys: prefix and tree
+  int32_t tiles, full;           // row tiles, and how many of them are full
+  int32_t last_live;             // live waves of the last, partial one (0: none)
+  int32_t floor_rows;            // rows of a tile, for chunk_keys()
+  double share;                  // of a chunk's K/V bytes that one tile streams from HBM
+  int64_t head_tiles;            // kv-heads * row tiles
+  double chunk_partials;         // bytes of split-KV partials of one chunk
+};
+
+// `kv_bytes`: what the batch's units stream of K and V, however it is split.
+static std::vector<PlanRequest> plan_requests(int32_t B, const int32_t *indptr_host, const int32_t *plen_host,
+                                              int32_t hkv, int32_t group, int32_t head_dim, double &kv_bytes) {
+  constexpr int32_t rt = kMaxRowsPerTile;
   const double key_bytes = 4.0 * head_dim;  // bf16 K and V of one key of one kv-head
-  double kv_bytes = 0, partial_bytes = 0;
-  int32_t longest = 0;
-  units.clear();
+  std::vector<PlanRequest> reqs(B);
+  kv_bytes = 0;
   for (int32_t r = 0; r < B; ++r) {
+    PlanRequest &q = reqs[r];
     const int32_t n = indptr_host[r + 1] - indptr_host[r];
-    const int32_t L = plen_host[r];
     const int32_t rows = n * group;
-    const int32_t tiles = row_tiles(n, group, rows_per_tile);
-    const int32_t chunks = prefix_chunks(L, ck[r]);
-    p.units += (int64_t)hkv * tiles * chunks;
-    p.row_groups += (int64_t)hkv * tiles;
-    kv_bytes += (double)hkv * (1.0 + kTileReread * (tiles - 1)) * (L + n) * key_bytes;
-    if (chunks > 1) {
-      p.needs_combine = true;
-      partial_bytes += hkv * chunks * (double)rows * (head_dim * 2.0 + 8.0);
+    q.blocks = ceil_div(plen_host[r], kKeysPerBlock);
+    q.tree_blocks = ceil_div(n, kKeysPerBlock);
+    q.tiles = row_tiles(n, group, rt);
+    q.full = rows / rt;
+    q.last_live = ceil_div(rows % rt, 32);
+    q.floor_rows = std::min(rows, rt);
+    const double streamed = 1.0 + kTileReread * (q.tiles - 1);
+    q.share = streamed / q.tiles;
+    q.head_tiles = (int64_t)hkv * q.tiles;
+    q.chunk_partials = hkv * (double)rows * (head_dim * 2.0 + 8.0);
+    kv_bytes += (double)hkv * streamed * (plen_host[r] + n) * key_bytes;
+  }
+  return reqs;
+}
+
+// One choice of chunk lengths and what it costs apart from its steps.
+struct PlanChoice {
+  size_t ck;            // its chunk lengths, as an offset
+  int32_t fm, c;        // batch-wide family (fm = 0: balanced)
+  int64_t units;
+  bool split;
+  double stream, fixed; // streaming time (K/V plus the split partials); kCallUs and the merge
+  double bound;         // a lower bound of the estimate
+};
+
+// Prices the choice of chunk lengths `ck` (prefix keys per unit, whole 32-key
+// blocks, at most kMaxChunk) with 128-row tiles.  The estimate is `fixed` plus
+// the larger of `stream` and the steps' time (steps_us); `bound` puts a lower
+// bound in the place of the latter: in one round the longest unit beside the
+// shortest, in several the longest unit, the rounds of the shortest, or the
+// mean load of the slots.
+static PlanChoice price_choice(const std::vector<PlanRequest> &reqs, const int32_t *ck, int32_t head_dim,
+                               double kv_bytes) {
+  PlanChoice p{};
+  double partial_bytes = 0;
+  int32_t longest = 0, shortest = INT32_MAX;
+  int64_t steps_total = 0;
+  for (size_t r = 0; r < reqs.size(); ++r) {
+    const PlanRequest &q = reqs[r];
+    const int32_t per_chunk = ck[r] / kKeysPerBlock;
+    int32_t steps;
+    if (q.blocks <= per_chunk) {
+      steps = q.blocks + q.tree_blocks;
+      p.units += q.head_tiles;
+      steps_total += q.head_tiles * steps;
+    } else {
+      const int32_t chunks = quick_ceil_div(q.blocks, per_chunk);
+      steps = per_chunk + tree_steps(q.tree_blocks, chunks);
+      p.split = true;
+      partial_bytes += chunks * q.chunk_partials;
+      p.units += q.head_tiles * chunks;
+      steps_total += q.head_tiles * chunks * steps;
     }
-    // the tree block is spread over the chunks
-    const int32_t steps = ceil_div(std::min(L, ck[r]), 32) + ceil_div(ceil_div(n, 32), chunks);
     longest = std::max(longest, steps);
-    const int32_t full = rows / rows_per_tile, last = rows % rows_per_tile;
-    const double share = (1.0 + kTileReread * (tiles - 1)) / tiles;
-    if (full > 0) units.push_back({steps, rows_per_tile / 32, share, (int64_t)hkv * chunks * full});
-    if (last > 0) units.push_back({steps, ceil_div(last, 32), share, (int64_t)hkv * chunks});
+    shortest = std::min(shortest, steps);
   }
   const double alone = (double)std::min<int64_t>(p.units, kCUs);
   const double paired = (double)std::min<int64_t>(std::max<int64_t>(p.units - kCUs, 0), kCUs);
-  const double rate = head_dim == 64 || p.units > kSlots ? kChipBytesPerUs * (alone + paired) / kSlots
-                                                         : alone * kCuBytesPerUs + paired * kPairBytesPerUs;
-  fixed = kCallUs + (p.needs_combine ? kCombineUs + partial_bytes / rate : 0.0);
-  p.est_us = (kv_bytes + partial_bytes) / rate;  // completed with the steps' time by make_plan
-  bound = std::max(p.est_us, longest * kStepUs) + fixed;
-  p.padded_grid = pad_to_xcds(p.units);
-  if (p.needs_combine) {
-    p.ws_o_bytes = round_up((size_t)p.units * kMaxRowsPerTile * head_dim * 2, 256);  // bf16
-    p.ws_ml_bytes = round_up((size_t)p.units * kMaxRowsPerTile * 2 * sizeof(float), 256);
-    p.ws_bytes = p.ws_o_bytes + p.ws_ml_bytes;
+  const bool one_round = head_dim != 64 && p.units <= kSlots;
+  const double rate = one_round ? alone * kCuBytesPerUs + paired * kPairBytesPerUs
+                                : kChipBytesPerUs * (alone + paired) / kSlots;
+  p.fixed = kCallUs + (p.split ? kCombineUs + partial_bytes / rate : 0.0);
+  p.stream = (kv_bytes + partial_bytes) / rate;
+  double steps_bound;
+  if (one_round) {
+    steps_bound = longest * kStepUs + (p.units > kCUs ? shortest * (kPairUs + kPairWaveUs) * kShortClock : 0.0) +
+                  kUnitStartUs * std::max<int64_t>(0, p.units - kFreeStarts);
+  } else {
+    const int64_t rounds = (p.units + kSlots - 1) / kSlots;   // units of the busiest slot, at least
+    steps_bound = std::max({kUnitFixedUs + longest * kBlockUs, rounds * (kUnitFixedUs + shortest * kBlockUs),
+                            (kUnitFixedUs * (double)p.units + (double)steps_total * kBlockUs) / kSlots});
   }
+  p.bound = std::max(p.stream, steps_bound) + p.fixed;
   return p;
+}
+
+// The units of a choice in descending order of steps (requests of equal steps
+// in their order), for steps_us.
+static void list_units(const std::vector<PlanRequest> &reqs, const int32_t *ck, int32_t hkv, PricingScratch &w) {
+  constexpr int32_t kMost = (kMaxChunk + kMaxTreeNodes) / kKeysPerBlock;   // steps of a unit
+  int32_t at[kMost + 2] = {};
+  const size_t B = reqs.size();
+  w.steps.resize(B);
+  w.chunks.resize(B);
+  for (size_t r = 0; r < B; ++r) {
+    const PlanRequest &q = reqs[r];
+    const int32_t per_chunk = ck[r] / kKeysPerBlock;
+    const int32_t chunks = q.blocks <= per_chunk ? 1 : quick_ceil_div(q.blocks, per_chunk);
+    const int32_t steps = std::min(q.blocks, per_chunk) + tree_steps(q.tree_blocks, chunks);
+    w.chunks[r] = chunks;
+    w.steps[r] = steps;
+    at[kMost - steps + 1] += (q.full > 0) + (q.last_live > 0);
+  }
+  for (int32_t i = 0; i <= kMost; ++i) at[i + 1] += at[i];
+  w.units.resize(at[kMost + 1]);
+  for (size_t r = 0; r < B; ++r) {
+    const PlanRequest &q = reqs[r];
+    const int64_t each = (int64_t)hkv * w.chunks[r];
+    int32_t &i = at[kMost - w.steps[r]];
+    if (q.full > 0) w.units[i++] = {w.steps[r], kMaxRowsPerTile / 32, q.share, each * q.full};
+    if (q.last_live > 0) w.units[i++] = {w.steps[r], q.last_live, q.share, each};
+  }
+}
+
+double estimate_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_host, int32_t hkv, int32_t group,
+                     int32_t head_dim, const int32_t *chunk_len) {
+  double kv_bytes;
+  const std::vector<PlanRequest> reqs = plan_requests(B, indptr_host, plen_host, hkv, group, head_dim, kv_bytes);
+  const PlanChoice c = price_choice(reqs, chunk_len, head_dim, kv_bytes);
+  PricingScratch w;
+  list_units(reqs, chunk_len, hkv, w);
+  return std::max(c.stream, steps_us(w, c.units, head_dim, HUGE_VAL)) + c.fixed;
 }
 
 // Work plan of the F32 kernel: 32-row tiles when they alone give every CU a
@@ -289,101 +422,159 @@ static AttnPlan make_f32_plan(int32_t B, const int32_t *indptr_host, int32_t hkv
 //    blocks no longer than the batch's mean blocks per unit, so the units
 //    come out about equally long and fill the workgroup slots evenly.
 // Choices that give every request the same chunk lengths as one already
-// tried are skipped, and the makespan is only simulated for choices whose
-// lower bound can still beat the best estimate so far.  Requests are then
-// dispatched in descending order of per-unit cost (fill_plan_table).
+// tried, or split nothing as one did, are skipped, and the steps are only timed for choices whose lower
+// bound can still be taken.  Requests are then dispatched in descending order
+// of per-unit cost (fill_plan_table).
 AttnPlan make_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_host, int32_t hkv,
                    int32_t group, int32_t head_dim, int32_t dtype) {
   AttnPlan best;
   if (B == 0) return best;
   if (dtype != ADASERVE_BF16) return make_f32_plan(B, indptr_host, hkv, group);
-  const int32_t rt = kMaxRowsPerTile;
-  struct Cand {
-    double bound;
-    int32_t fm, c;   // batch-wide family (fm = 0: balanced)
-    std::vector<int32_t> ck;
-  };
-  std::vector<Cand> cands;
-  std::vector<UnitRun> units;
-  double fixed, bound;
-  auto add = [&](int32_t fm, int32_t c, std::vector<int32_t> ck) {
-    for (const Cand &x : cands)
-      if (x.ck == ck) return;
-    evaluate_plan(B, indptr_host, plen_host, hkv, group, head_dim, rt, ck, units, fixed, bound);
-    cands.push_back({bound, fm, c, std::move(ck)});
-  };
-  std::vector<int32_t> ck(B);
-  for (int32_t fm : {32, 16, 8})
-    for (int32_t c = kMaxChunk; c >= kMinChunk; c /= 2) {
-      for (int32_t r = 0; r < B; ++r) ck[r] = chunk_keys(indptr_host[r + 1] - indptr_host[r], group, rt, c, fm);
-      add(fm, c, ck);
-    }
-  if (B <= kPlanMax) {
-    int64_t work = 0;   // unit-blocks of the unsplit batch
-    for (int32_t r = 0; r < B; ++r)
-      work += (int64_t)hkv * row_tiles(indptr_host[r + 1] - indptr_host[r], group, rt) *
-              std::max(1, ceil_div(plen_host[r], kKeysPerBlock));
-    for (int32_t target : {160, 192, 224, 256, 288, 320, 352, 384, 416, 448, 512, 576, 640, 768, 1024}) {
-      const int64_t per_unit = std::max<int64_t>(4, (work + target - 1) / target);
-      for (int32_t r = 0; r < B; ++r) {
-        const int32_t blocks = ceil_div(std::max(plen_host[r], 0), kKeysPerBlock);
-        if (blocks == 0) {
-          ck[r] = kMaxChunk;
-          continue;
-        }
-        const int32_t runs = (int32_t)std::max<int64_t>((blocks + per_unit - 1) / per_unit,
-                                                        ceil_div(blocks, kMaxChunk / kKeysPerBlock));
-        ck[r] = ceil_div(blocks, runs) * kKeysPerBlock;
+  constexpr int32_t rt = kMaxRowsPerTile;
+  constexpr int32_t kFloors[] = {32, 16, 8};
+  constexpr int32_t kTargets[] = {160, 192, 224, 256, 288, 320, 352, 384, 416, 448, 512, 576, 640, 768, 1024};
+  double kv_bytes;
+  const std::vector<PlanRequest> reqs = plan_requests(B, indptr_host, plen_host, hkv, group, head_dim, kv_bytes);
+  int64_t work = 0;   // unit-blocks of the unsplit batch
+  for (const PlanRequest &q : reqs) work += q.head_tiles * std::max(1, q.blocks);
+
+  std::vector<PlanChoice> choices;
+  choices.reserve(std::size(kFloors) * 6 + std::size(kTargets));
+  std::vector<int32_t> cks;   // chunk lengths of all choices, and of the one being made
+  cks.reserve((choices.capacity() + 1) * B);
+  auto add = [&](int32_t fm, int32_t c) {
+    const int32_t *ck = cks.data() + cks.size() - B;
+    PlanChoice p = price_choice(reqs, ck, head_dim, kv_bytes);
+    for (const PlanChoice &x : choices)
+      if (x.units == p.units && x.bound == p.bound &&
+          ((!x.split && !p.split) || std::equal(ck, ck + B, cks.data() + x.ck))) {
+        cks.resize(cks.size() - B);
+        return;
       }
-      add(0, 0, ck);
+    p.ck = cks.size() - B;
+    p.fm = fm;
+    p.c = c;
+    choices.push_back(p);
+  };
+  int32_t longest_prefix = 0;
+  for (const PlanRequest &q : reqs) longest_prefix = std::max(longest_prefix, q.blocks * kKeysPerBlock);
+  bool unsplit = false;   // one choice that splits nothing is enough
+  auto splits_nothing_again = [&](int32_t chunk) { return chunk >= longest_prefix && std::exchange(unsplit, true); };
+  std::vector<int32_t> floor_ck(B);
+  int32_t above = INT32_MAX;   // from this target on the floors have no effect: the same as with the last floor
+  for (int32_t fm : kFloors) {
+    int32_t least_floor = INT32_MAX, most_floor = 0;
+    for (int32_t r = 0; r < B; ++r) {
+      floor_ck[r] = chunk_keys(1, reqs[r].floor_rows, rt, 0, fm);
+      least_floor = std::min(least_floor, floor_ck[r]);
+      most_floor = std::max(most_floor, floor_ck[r]);
+    }
+    for (int32_t c = kMaxChunk; c >= kMinChunk; c /= 2) {
+      if (c >= above || 2 * c <= least_floor || splits_nothing_again(c)) continue;
+      for (int32_t r = 0; r < B; ++r) cks.push_back(std::max(floor_ck[r], c));
+      add(fm, c);
+    }
+    above = most_floor;
+  }
+  if (B <= kPlanMax) {
+    int32_t last = 0;
+    for (int32_t target : kTargets) {
+      const int32_t per_unit =
+          (int32_t)std::min<int64_t>(std::max<int64_t>(4, (work + target - 1) / target), kMaxChunk / kKeysPerBlock);
+      if (per_unit == last || splits_nothing_again(per_unit * kKeysPerBlock)) continue;
+      last = per_unit;
+      for (const PlanRequest &q : reqs)
+        cks.push_back(q.blocks == 0 ? kMaxChunk
+                                    : quick_ceil_div(q.blocks, quick_ceil_div(q.blocks, per_unit)) * kKeysPerBlock);
+      add(0, 0);
     }
   }
+  std::vector<std::pair<double, size_t>> order;   // (bound, choice), ascending
+  order.reserve(choices.size());
+  for (size_t i = 0; i < choices.size(); ++i) order.push_back({choices[i].bound, i});
+  std::sort(order.begin(), order.end());
+
   // The cheapest estimate wins; at head_dim 128, among plans of more than a
   // unit per CU within kTie of it (what the estimate is good for), the one of
   // fewest units: it has less to merge, and in the one-call step the argmax
   // rows find free slots from the start.  (Step of the 8B batch: 512 units
   // 66.2 us, 464 64.2, 440 59.5, 416 58-59; its attention alone 36-39 for all.)
+  constexpr double kTie = 1.1;
+  PricingScratch w;
+  std::vector<double> ests(choices.size(), 0.0);   // 0: not priced yet
+  // The estimate of choice i, or something past `limit` when it is past that.
+  auto estimate = [&](size_t i, double limit) {
+    if (ests[i] == 0.0) {
+      const PlanChoice &c = choices[i];
+      list_units(reqs, cks.data() + c.ck, hkv, w);
+      const double est = std::max(c.stream, steps_us(w, c.units, head_dim, limit - c.fixed)) + c.fixed;
+      if (est > limit) return est;
+      ests[i] = est;
+    }
+    return ests[i];
+  };
+  auto fits = [&](const PlanChoice &c) {
+    return !c.split || partial_bytes(c.units, head_dim) <= ADASERVE_TREE_ATTN_SCRATCH_BYTES;
+  };
+  constexpr size_t kNone = SIZE_MAX;
+  // The choice taken (of those whose partials fit the static scratch, with
+  // `fit_only`; kNone when none does) and the least estimate.
+  auto select = [&](bool fit_only, double &least) {
+    size_t pick = kNone;
+    for (const auto &[bound, i] : order) {
+      if (pick != kNone && bound >= ests[pick]) break;   // none of the rest is cheaper
+      if (fit_only && !fits(choices[i])) continue;
+      const double most = pick == kNone ? HUGE_VAL : ests[pick];
+      if (estimate(i, most) < most) pick = i;
+    }
+    if (pick == kNone) return pick;
+    least = ests[pick];
+    if (head_dim != 128 || choices[pick].units <= kCUs) return pick;
+    const double tie = least * kTie;
+    std::vector<std::pair<int64_t, size_t>> fewer;   // (units, choice), ascending
+    for (const auto &[bound, i] : order)
+      if (bound <= tie && choices[i].units > kCUs && choices[i].units < choices[pick].units &&
+          (!fit_only || fits(choices[i])))
+        fewer.push_back({choices[i].units, i});
+    std::sort(fewer.begin(), fewer.end());
+    size_t fewest = kNone;
+    for (const auto &[few, i] : fewer) {
+      if (fewest != kNone && few > choices[fewest].units) break;
+      const double most = fewest == kNone ? tie : ests[fewest];
+      if (estimate(i, most) <= most && (fewest == kNone || ests[i] < ests[fewest])) fewest = i;
+    }
+    return fewest == kNone ? pick : fewest;
+  };
+  double least = 0;
+  size_t pick = select(false, least);
   // A plan whose partials fit the static scratch is taken even at kScratchCost
   // times the estimate, so that the allocation-free call can run the batch.
-  constexpr double kTie = 1.1, kScratchCost = 1.6;
-  std::stable_sort(cands.begin(), cands.end(), [](const Cand &x, const Cand &y) { return x.bound < y.bound; });
-  struct Priced {
-    size_t cand;
-    double est;
-    int64_t units;
-    bool fits;   // its partials fit the static scratch
-  };
-  std::vector<Priced> priced;
-  double least = 0, least_fit = 0;   // 0: none yet
-  for (size_t i = 0; i < cands.size(); ++i) {
-    if (least > 0 && cands[i].bound >= least * kScratchCost) break;
-    if (least_fit > 0 && cands[i].bound >= least_fit * kTie) break;
-    const AttnPlan p =
-        evaluate_plan(B, indptr_host, plen_host, hkv, group, head_dim, rt, cands[i].ck, units, fixed, bound);
-    const double est = std::max(p.est_us, steps_us(units, p.units, head_dim)) + fixed;
-    const bool fits = p.ws_bytes <= ADASERVE_TREE_ATTN_SCRATCH_BYTES;
-    priced.push_back({i, est, p.units, fits});
-    if (least == 0 || est < least) least = est;
-    if (fits && (least_fit == 0 || est < least_fit)) least_fit = est;
+  constexpr double kScratchCost = 1.6;
+  if (!fits(choices[pick])) {
+    double least_fit = 0;
+    const size_t fit = select(true, least_fit);
+    if (fit != kNone && least_fit <= least * kScratchCost) pick = fit;
   }
-  const bool use_fit = least_fit > 0 && least_fit <= least * kScratchCost;
-  const Priced *pick = nullptr;
-  for (const Priced &x : priced)
-    if ((x.fits || !use_fit) && (!pick || x.est < pick->est)) pick = &x;
-  if (head_dim == 128 && pick->units > kCUs) {
-    const double tie = pick->est * kTie;
-    for (const Priced &x : priced)
-      if ((x.fits || !use_fit) && x.est <= tie && x.units > kCUs && x.units < pick->units) pick = &x;
+  const PlanChoice &chosen = choices[pick];
+  best.rows_per_tile = rt;
+  best.chunk_len.assign(cks.begin() + chosen.ck, cks.begin() + chosen.ck + B);
+  best.units = chosen.units;
+  best.padded_grid = pad_to_xcds(best.units);
+  best.needs_combine = chosen.split;
+  if (best.needs_combine) {
+    best.ws_o_bytes = partial_rows_bytes(best.units, head_dim);
+    best.ws_bytes = partial_bytes(best.units, head_dim);
+    best.ws_ml_bytes = best.ws_bytes - best.ws_o_bytes;
   }
-  const Cand &chosen = cands[pick->cand];
-  best = evaluate_plan(B, indptr_host, plen_host, hkv, group, head_dim, rt, chosen.ck, units, fixed, bound);
-  best.est_us = pick->est;
+  best.est_us = ests[pick];
   // the batch-wide fields rebuild the chunks when there is no plan table
   best.chunk_target = chosen.fm ? chosen.c : kMaxChunk;
   best.chunk_floor = chosen.fm ? chosen.fm : 32;
   best.single_tile = true;
-  for (int32_t r = 0; r < B; ++r)
-    best.single_tile &= row_tiles(indptr_host[r + 1] - indptr_host[r], group, rt) == 1;
+  for (const PlanRequest &q : reqs) {
+    best.row_groups += q.head_tiles;
+    best.single_tile &= q.tiles == 1;
+  }
   return best;
 }
 

@@ -53,6 +53,27 @@ size_t round_up(size_t x, size_t a);
 // `units` holds (duration, count) pairs and is sorted in place.
 double lpt_makespan(std::vector<std::pair<double, int64_t>> &units);
 
+// Equal units: 32-key steps and live waves of each, the share of their K/V bytes
+// that other tiles do not stream, and their number.
+struct UnitRun {
+  int32_t steps, live;
+  double share;
+  int64_t count;
+};
+
+// The time of one CU's units: `first` alone, or with `second` beside it.
+double pair_us(const UnitRun &first, const UnitRun *second);
+
+// Time of the steps of `total` units, at most two per CU, given in descending
+// order of steps: the longest pair when unit i shares a CU with unit (CUs + i),
+// and what the units' starts cost each other.
+double one_round_us(const std::vector<UnitRun> &units, int64_t total);
+
+// The bf16 planner's estimate of the call with these chunk lengths (prefix keys
+// per unit of each request, whole 32-key blocks, at most kMaxChunk).
+double estimate_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_host, int32_t hkv, int32_t group,
+                     int32_t head_dim, const int32_t *chunk_len);
+
 // Work plan of a validated batch (host sizes only); an empty plan (no units)
 // for an empty batch.  F32 plans split no prefix and need no workspace.
 AttnPlan make_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_host, int32_t hkv,

@@ -150,6 +150,65 @@ static bool same_plan(const AttnPlan &x, const AttnPlan &y) {
          x.ws_ml_bytes == y.ws_ml_bytes && x.ws_bytes == y.ws_bytes && x.est_us == y.est_us;
 }
 
+// The planner's choice against every choice of its two families, each made with
+// integer divisions and priced in full: none is estimated much cheaper.  (The
+// planner prices few of them in full, by lower bounds, and divides in floats.)
+static void check_choice(const Batch &b, int hkv, int G, int D) {
+  const int B = (int)b.plen.size();
+  const int *ip = b.indptr.data(), *pl = b.plen.data();
+  const AttnPlan p = make_plan(B, ip, pl, hkv, G, D, ADASERVE_BF16);
+  CHECK(p.est_us == estimate_plan(B, ip, pl, hkv, G, D, p.chunk_len.data()), "estimate %g", p.est_us);
+  double least = INFINITY;
+  std::vector<int32_t> ck(B);
+  auto price = [&]() { least = std::min(least, estimate_plan(B, ip, pl, hkv, G, D, ck.data())); };
+  for (int fm : {8, 16, 32})
+    for (int c = kMinChunk; c <= kMaxChunk; c *= 2) {
+      for (int r = 0; r < B; ++r) ck[r] = chunk_keys(ip[r + 1] - ip[r], G, kMaxRowsPerTile, c, fm);
+      price();
+    }
+  if (B <= kPlanMax) {
+    int64_t work = 0;
+    for (int r = 0; r < B; ++r)
+      work += (int64_t)hkv * row_tiles(ip[r + 1] - ip[r], G, kMaxRowsPerTile) * std::max(1, ceil_div(pl[r], 32));
+    for (int target : {160, 192, 224, 256, 288, 320, 352, 384, 416, 448, 512, 576, 640, 768, 1024}) {
+      const int64_t per_unit = std::max<int64_t>(4, (work + target - 1) / target);
+      for (int r = 0; r < B; ++r) {
+        const int64_t blocks = ceil_div(pl[r], 32);
+        const int64_t runs = std::max<int64_t>((blocks + per_unit - 1) / per_unit, (blocks + 255) / 256);
+        ck[r] = blocks == 0 ? kMaxChunk : (int32_t)((blocks + runs - 1) / runs) * 32;
+      }
+      price();
+    }
+  }
+  // within 10% for fewer units; further off only for partials that fit the scratch
+  const bool fits = p.ws_bytes <= ADASERVE_TREE_ATTN_SCRATCH_BYTES;
+  CHECK(p.est_us <= least * (fits ? 1.6 * 1.1 : 1.1) * (1 + 1e-12), "%g us, least %g", p.est_us, least);
+}
+
+// One round of units, two per CU, unit by unit.
+static void check_one_round(std::mt19937_64 &rng) {
+  for (int it = 0; it < 400; ++it) {
+    std::vector<UnitRun> runs;
+    std::vector<UnitRun> each;
+    const int most = 1 + (int)(rng() % 512);
+    int total = 0, steps = 260;
+    while (total < most) {
+      steps = std::max(1, steps - (int)(rng() % 40));
+      const int count = std::min(most - total, 1 + (int)(rng() % (it % 2 ? 300 : 12)));
+      runs.push_back({steps, 1 + (int)(rng() % 4), 0.5 + (double)(rng() % 8) / 16, count});
+      total += count;
+      for (int i = 0; i < count; ++i) each.push_back(runs.back());
+    }
+    double worst = 0;
+    for (int i = 0; i < std::min(total, 256); ++i)
+      worst = std::max(worst, pair_us(each[i], i + 256 < total ? &each[i + 256] : nullptr));
+    const UnitRun tiny{1, 1, 0.0, total};
+    // what the starts add is the same for any units
+    const double start = one_round_us({tiny}, total) - pair_us(tiny, total > 256 ? &tiny : nullptr);
+    CHECK(std::fabs(one_round_us(runs, total) - start - worst) < 1e-9, "round of %d units", total);
+  }
+}
+
 // The cached planner against a fresh plan on every call of a sequence that
 // repeats batches, refills the same buffers in place (one prefix grows by a
 // token, one tree loses a node) and changes only a scalar argument.
@@ -202,12 +261,14 @@ int main() {
     const int B = 1 + (int)(rng() % (it % 5 == 0 ? 300 : 64));
     const Batch b = random_batch(rng, B, it % 3 ? 128 : 8, it % 4 ? 20000 : 200000);
     check_plan(b, h[0], h[1], it % 2 ? 128 : 64);
+    if (it % 3 == 0) check_choice(b, h[1], h[0] / h[1], it % 2 ? 128 : 64);
   }
   {
     Batch b;  // the longest prefixes the validation accepts, the largest trees
     b.indptr = {0, 128, 256};
     b.plen = {kMaxPrefixLen, kMaxPrefixLen - 31};
     check_plan(b, 32, 2, 128);
+    check_choice(b, 2, 16, 128);
     check_plan(b, 128, 8, 64);
   }
   {
@@ -220,9 +281,11 @@ int main() {
         b.plen.push_back(r * 97);
       }
       check_plan(b, 32, 8, 128);
+      check_choice(b, 8, 4, 128);
     }
   }
   check_plan_cache(rng);
+  check_one_round(rng);
   // the makespan model against brute-force dealing
   for (int it = 0; it < 300; ++it) {
     std::vector<std::pair<double, int64_t>> u;
