@@ -145,12 +145,14 @@ int32_t adaserve_tree_attn_verify(int32_t num_requests, const int32_t *node_indp
  * allocator of any kind.
  *
  * Arguments, layouts, results and errors are those of
- * adaserve_tree_attn_verify (same plan, same kernels, bit-identical output);
- * the split-KV partial results go to a static array of
- * ADASERVE_TREE_ATTN_SCRATCH_BYTES bytes that the library holds on every
- * device it runs on until the process ends.  A batch whose plan needs more
- * than that (adaserve_tree_attn_workspace_bytes(...) > the limit) is
- * rejected with ADASERVE_ERR_WORKSPACE before anything is enqueued.  Every
+ * adaserve_tree_attn_verify; the split-KV partial results go to a static
+ * array of ADASERVE_TREE_ATTN_SCRATCH_BYTES bytes that the library holds on
+ * every device it runs on until the process ends.  A batch whose partials fit
+ * it (adaserve_tree_attn_workspace_bytes(...) <= the limit) runs with the same
+ * plan and kernels, bit-identical to adaserve_tree_attn_verify.  A batch whose
+ * partials do not is split more coarsely, where a split that fits is not
+ * estimated much slower (BF16 results then differ by rounding), and is otherwise rejected
+ * with ADASERVE_ERR_WORKSPACE before anything is enqueued.  Every
  * call on one device shares that device's array: calls that overlap in time
  * on one device (other streams, other threads) race and give undefined
  * results; calls on one stream are ordered and safe.  The array's contents

@@ -171,8 +171,11 @@ int32_t tree_attn_verify_impl(int32_t num_requests, const int32_t *node_indptr, 
   const void *tensors[] = {q, k_tree, v_tree, out, k_pages, v_pages};
   for (const void *t : tensors)
     if (t && !aligned(t, 16)) return fail(ADASERVE_ERR_INVALID_ARGUMENT, "tensor pointers must be 16-byte aligned");
-  const AttnPlan plan =
+  AttnPlan plan =
       make_plan_cached(num_requests, node_indptr_host, prefix_len_host, num_kv_heads, shape.group, head_dim, dtype);
+  if (use_scratch && plan.ws_bytes > (size_t)ADASERVE_TREE_ATTN_SCRATCH_BYTES)
+    plan = make_plan_cached(num_requests, node_indptr_host, prefix_len_host, num_kv_heads, shape.group, head_dim, dtype,
+                            true);
   if (use_scratch) {
     if (plan.ws_bytes > (size_t)ADASERVE_TREE_ATTN_SCRATCH_BYTES)
       return fail(ADASERVE_ERR_WORKSPACE,

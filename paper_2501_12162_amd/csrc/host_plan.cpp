@@ -426,7 +426,7 @@ static AttnPlan make_f32_plan(int32_t B, const int32_t *indptr_host, int32_t hkv
 // bound can still be taken.  Requests are then dispatched in descending order
 // of per-unit cost (fill_plan_table).
 AttnPlan make_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_host, int32_t hkv,
-                   int32_t group, int32_t head_dim, int32_t dtype) {
+                   int32_t group, int32_t head_dim, int32_t dtype, bool in_scratch) {
   AttnPlan best;
   if (B == 0) return best;
   if (dtype != ADASERVE_BF16) return make_f32_plan(B, indptr_host, hkv, group);
@@ -518,8 +518,8 @@ AttnPlan make_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_ho
   };
   constexpr size_t kNone = SIZE_MAX;
   // The choice taken (of those whose partials fit the static scratch, with
-  // `fit_only`; kNone when none does) and the least estimate.
-  auto select = [&](bool fit_only, double &least) {
+  // `fit_only`; kNone when none does), and the one of the least estimate.
+  auto select = [&](bool fit_only, size_t &cheapest) {
     size_t pick = kNone;
     for (const auto &[bound, i] : order) {
       if (pick != kNone && bound >= ests[pick]) break;   // none of the rest is cheaper
@@ -527,10 +527,10 @@ AttnPlan make_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_ho
       const double most = pick == kNone ? HUGE_VAL : ests[pick];
       if (estimate(i, most) < most) pick = i;
     }
+    cheapest = pick;
     if (pick == kNone) return pick;
-    least = ests[pick];
     if (head_dim != 128 || choices[pick].units <= kCUs) return pick;
-    const double tie = least * kTie;
+    const double tie = ests[pick] * kTie;
     std::vector<std::pair<int64_t, size_t>> fewer;   // (units, choice), ascending
     for (const auto &[bound, i] : order)
       if (bound <= tie && choices[i].units > kCUs && choices[i].units < choices[pick].units &&
@@ -545,15 +545,19 @@ AttnPlan make_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_ho
     }
     return fewest == kNone ? pick : fewest;
   };
-  double least = 0;
-  size_t pick = select(false, least);
-  // A plan whose partials fit the static scratch is taken even at kScratchCost
-  // times the estimate, so that the allocation-free call can run the batch.
+  size_t cheapest = kNone;
+  size_t pick = select(false, cheapest);
+  // Plans whose partials fit the static scratch are taken as long as the least
+  // estimate of them ties with the least of all, and by a call that has only
+  // the scratch at up to kScratchCost times that.  (At a tie the estimates do
+  // not tell which is faster, measured 0.91-1.11 either way; at 1.27 times,
+  // 65 requests of 1-8 nodes over 6600 keys, 64 / 8 heads, 350 | 325 us with a
+  // workspace.)
   constexpr double kScratchCost = 1.6;
-  if (!fits(choices[pick])) {
-    double least_fit = 0;
-    const size_t fit = select(true, least_fit);
-    if (fit != kNone && least_fit <= least * kScratchCost) pick = fit;
+  if (!fits(choices[cheapest])) {   // if it fits, so does a tie of fewer units
+    size_t cheapest_fit = kNone;
+    const size_t fit = select(true, cheapest_fit);
+    if (fit != kNone && ests[cheapest_fit] <= ests[cheapest] * (in_scratch ? kScratchCost : kTie)) pick = fit;
   }
   const PlanChoice &chosen = choices[pick];
   best.rows_per_tile = rt;
@@ -579,7 +583,7 @@ AttnPlan make_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_ho
 }
 
 AttnPlan make_plan_cached(int32_t B, const int32_t *indptr_host, const int32_t *plen_host, int32_t hkv,
-                          int32_t group, int32_t head_dim, int32_t dtype) {
+                          int32_t group, int32_t head_dim, int32_t dtype, bool in_scratch) {
   if (dtype != ADASERVE_BF16 || B <= 0) return make_plan(B, indptr_host, plen_host, hkv, group, head_dim, dtype);
   struct Entry {
     bool valid = false;
@@ -587,13 +591,14 @@ AttnPlan make_plan_cached(int32_t B, const int32_t *indptr_host, const int32_t *
     std::vector<int32_t> indptr, plen;
     AttnPlan plan;
   };
-  thread_local Entry e;
+  thread_local Entry entries[2];
+  Entry &e = entries[in_scratch];
   const bool hit = e.valid && e.B == B && e.hkv == hkv && e.group == group && e.head_dim == head_dim &&
                    e.dtype == dtype && std::equal(indptr_host, indptr_host + B + 1, e.indptr.begin()) &&
                    std::equal(plen_host, plen_host + B, e.plen.begin());
   if (!hit) {
     e.valid = false;
-    e.plan = make_plan(B, indptr_host, plen_host, hkv, group, head_dim, dtype);
+    e.plan = make_plan(B, indptr_host, plen_host, hkv, group, head_dim, dtype, in_scratch);
     e.indptr.assign(indptr_host, indptr_host + B + 1);
     e.plen.assign(plen_host, plen_host + B);
     e.B = B;

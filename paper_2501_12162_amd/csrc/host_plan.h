@@ -76,16 +76,19 @@ double estimate_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_
 
 // Work plan of a validated batch (host sizes only); an empty plan (no units)
 // for an empty batch.  F32 plans split no prefix and need no workspace.
+// With `in_scratch`, a plan whose partials do not fit the static scratch gives
+// way to one whose partials do, when there is one at a bearable cost.
 AttnPlan make_plan(int32_t B, const int32_t *indptr_host, const int32_t *plen_host, int32_t hkv,
-                   int32_t group, int32_t head_dim, int32_t dtype);
+                   int32_t group, int32_t head_dim, int32_t dtype, bool in_scratch = false);
 
-// make_plan through a one-entry cache per thread, keyed by the scalar
-// arguments and the contents of both host mirrors (not their addresses: a
-// caller may refill the same buffers between calls).  The workspace query
+// make_plan through a cache per thread, of one entry for each value of
+// `in_scratch`, keyed by the scalar arguments and the contents of both host
+// mirrors (not their addresses: a caller may refill the same buffers between
+// calls).  The workspace query
 // and the verify call of one batch then plan it once, and a batch verified
 // again (a retried or repeated step) costs a comparison of 2B + 1 integers.
 AttnPlan make_plan_cached(int32_t B, const int32_t *indptr_host, const int32_t *plen_host, int32_t hkv,
-                          int32_t group, int32_t head_dim, int32_t dtype);
+                          int32_t group, int32_t head_dim, int32_t dtype, bool in_scratch = false);
 
 // The dispatch-ordered request table for batches of at most kPlanMax
 // requests (count = 0 otherwise).

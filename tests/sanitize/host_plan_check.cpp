@@ -153,6 +153,8 @@ static bool same_plan(const AttnPlan &x, const AttnPlan &y) {
 // The planner's choice against every choice of its two families, each made with
 // integer divisions and priced in full: none is estimated much cheaper.  (The
 // planner prices few of them in full, by lower bounds, and divides in floats.)
+static int scratch_plans = 0;   // batches planned otherwise for the scratch
+
 static void check_choice(const Batch &b, int hkv, int G, int D) {
   const int B = (int)b.plen.size();
   const int *ip = b.indptr.data(), *pl = b.plen.data();
@@ -180,9 +182,16 @@ static void check_choice(const Batch &b, int hkv, int G, int D) {
       price();
     }
   }
-  // within 10% for fewer units; further off only for partials that fit the scratch
+  // within 10% for partials that fit the scratch, and within 10% for fewer units
   const bool fits = p.ws_bytes <= ADASERVE_TREE_ATTN_SCRATCH_BYTES;
-  CHECK(p.est_us <= least * (fits ? 1.6 * 1.1 : 1.1) * (1 + 1e-12), "%g us, least %g", p.est_us, least);
+  CHECK(p.est_us <= least * (fits ? 1.1 * 1.1 : 1.1) * (1 + 1e-12), "%g us, least %g", p.est_us, least);
+  // in the scratch: the same plan if it fits, else one that does at a bearable
+  // cost, else the same plan (which the call refuses)
+  const AttnPlan s = make_plan(B, ip, pl, hkv, G, D, ADASERVE_BF16, true);
+  const bool same = s.chunk_len == p.chunk_len && s.ws_bytes == p.ws_bytes;
+  CHECK(same || (!fits && s.ws_bytes <= ADASERVE_TREE_ATTN_SCRATCH_BYTES && s.est_us <= least * 1.6 * 1.1 * (1 + 1e-12)),
+        "in the scratch: %zu bytes, %g us, least %g", s.ws_bytes, s.est_us, least);
+  scratch_plans += !same;
 }
 
 // One round of units, two per CU, unit by unit.
@@ -286,6 +295,19 @@ int main() {
   }
   check_plan_cache(rng);
   check_one_round(rng);
+  {
+    Batch b;  // in halves with a workspace, unsplit in the scratch
+    b.indptr = {0};
+    for (int r = 0; r < 65; ++r) b.indptr.push_back(b.indptr.back() + 5), b.plen.push_back(6630);
+    const int before = scratch_plans;
+    check_choice(b, 8, 8, 128);
+    CHECK(scratch_plans == before + 1, "the same plan");
+    // the two cache entries do not answer for each other
+    const AttnPlan w = make_plan_cached(65, b.indptr.data(), b.plen.data(), 8, 8, 128, ADASERVE_BF16);
+    const AttnPlan s = make_plan_cached(65, b.indptr.data(), b.plen.data(), 8, 8, 128, ADASERVE_BF16, true);
+    CHECK(!same_plan(w, s), "cached plans");
+    CHECK(same_plan(w, make_plan_cached(65, b.indptr.data(), b.plen.data(), 8, 8, 128, ADASERVE_BF16)), "cached plan");
+  }
   // the makespan model against brute-force dealing
   for (int it = 0; it < 300; ++it) {
     std::vector<std::pair<double, int64_t>> u;

@@ -159,6 +159,14 @@ def test_planning_a_new_batch_is_cheap(lib):
     assert best < 0.22
 
 
+def test_a_call_with_a_workspace_is_not_planned_for_the_scratch(lib):
+    """65 requests of 5 nodes over 6630 keys, 64 / 8 heads: unsplit, which needs
+    no partials, they make 520 long units for 512 places; in halves they are a
+    fifth faster, with more partials than the scratch holds.  The call with a
+    workspace gets the halves."""
+    assert _ws(np.arange(0, 66 * 5, 5), [6630] * 65, hq=64, hkv=8) > ada.TREE_ATTN_SCRATCH_BYTES
+
+
 def test_verify_noalloc_rejects_batches_past_the_scratch(lib):
     # a plan needing more split-KV partials than the static scratch holds is
     # refused before anything is enqueued, with the sizes in the message

@@ -62,6 +62,38 @@ def _noalloc(ada, d, out, stream=None):
         sm_scale=d.batch.sm_scale, out=out, stream=stream)
 
 
+@pytest.mark.parametrize("head_dim,sizes,lens", [
+    (64, [89, 65, 45, 23, 20, 84, 84], [80986, 79830, 48448, 51868, 86165, 61635, 90722]),
+    (128, [126] * 37, [1773] * 37),            # not split at all in the scratch
+])
+def test_noalloc_splits_more_coarsely_to_fit_the_scratch(head_dim, sizes, lens):
+    """A batch whose plan needs more partials than the scratch holds, and that
+    can be split into fewer: the workspace call runs the former, the
+    allocation-free call the latter, both within the oracle's bars."""
+    import torch
+    import paper_2501_12162_amd as ada
+    from paper_2501_12162_amd.device import DeviceBatch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    ada.load_library()
+    rng = np.random.Generator(np.random.PCG64(95))
+    b = make_batch(parents=[random_tree(rng, n) for n in sizes], prefix_lens=lens, num_q_heads=16, num_kv_heads=1,
+                   head_dim=head_dim, dtype="bf16", vocab=64, seed=95)
+    d = DeviceBatch(b)
+    assert d.workspace_bytes > ada.TREE_ATTN_SCRATCH_BYTES
+    d.attention()
+    out = torch.full_like(d.out, float("nan"))
+    print("noalloc call: requests", b.num_requests, "workspace", d.workspace_bytes, flush=True)
+    _noalloc(ada, d, out)
+    torch.cuda.synchronize()
+    some = np.sort(rng.choice(b.total_nodes, size=100, replace=False))
+    ref = oracle.tree_attn_batch(b, nodes=some)
+    for o in (d.out, out):
+        got = o.float().cpu().numpy()
+        assert np.isfinite(got).all()
+        err = float(np.abs(got[some] - ref).max())
+        assert err <= BF16_ABS and err <= BF16_REL * float(np.abs(ref).max()), err
+
+
 def test_noalloc_replayed_from_a_graph():
     """Captured in a HIP graph (what a caller that cannot allocate does) and
     replayed three times, the output poisoned before each replay and an eager
