@@ -637,7 +637,7 @@ void fill_plan_table(PlanTable &t, int32_t B, const int32_t *indptr_host, const 
     if (prefix_chunks(plen_host[r], p.chunk_len[r]) > 1) gend += (int64_t)num_kv_heads * ceil_div(n * group, 16);
     t.entry[i].unit_end = (int32_t)end;
     t.entry[i].group_end = (int32_t)gend;
-    t.entry[i].request_and_chunk = pack_request_chunk(r, p.chunk_len[r] / kKeysPerBlock);
+    t.entry[i].request_and_chunk = pack_request_chunk(r, p.chunk_len[r]);
     t.entry[i].node_base = indptr_host[r];
     t.entry[i].n_and_len = pack_nodes_len(n, plen_host[r]);
   }

@@ -2,7 +2,7 @@
 //
 // One work unit = (request r, kv-head g, row tile, prefix chunk).  The rows
 // of (r, g) are the N_r * G (node, q-head-in-group) pairs, row m = node *
-// G + head-in-group, cut into tiles of `rows_per_tile` rows (64 or 128).
+// G + head-in-group, cut into tiles of `rows_per_tile` rows (BF16: 128).
 // The prefix of r is cut into chunks of whole 32-key blocks, at most
 // kMaxChunk keys each: the chunk length of each request comes from the plan
 // table in the kernel arguments, or, for batches too large for the table,
@@ -87,10 +87,12 @@ struct PlanEntry {
 };
 
 // Field packing of a plan entry: request < kPlanMax, blocks per chunk <=
-// kMaxChunk / 32, tree nodes <= kMaxTreeNodes, prefix length < 2^23 (the
-// host validation's limit), so every field fits its bits.
-ADASERVE_HD int32_t pack_request_chunk(int32_t request, int32_t chunk_blocks) {
-  return (int32_t)((uint32_t)request | ((uint32_t)chunk_blocks << 16));
+// kMaxChunk / 32, tree nodes <= kMaxTreeNodes, prefix length < 2^23 (the host
+// validation's limit), so every field fits its bits.  An F32 unit's chunk, the
+// whole prefix (kF32Chunk), is stored as 0 and handed back as 0 keys.
+ADASERVE_HD int32_t pack_request_chunk(int32_t request, int32_t chunk_keys) {
+  const int32_t blocks = chunk_keys == kF32Chunk ? 0 : chunk_keys / kKeysPerBlock;
+  return (int32_t)((uint32_t)request | ((uint32_t)blocks << 16));
 }
 ADASERVE_HD int32_t plan_request(int32_t v) { return v & 0xffff; }
 ADASERVE_HD int32_t plan_chunk_keys(int32_t v) { return (int32_t)((uint32_t)v >> 16) * kKeysPerBlock; }

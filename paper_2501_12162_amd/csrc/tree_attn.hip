@@ -179,10 +179,10 @@ __device__ bool locate_request(int64_t idx, bool count_groups, const TreeAttnArg
 }
 
 // The work unit with logical id `uid`: its request, that request's sizes, the
-// prefix keys per unit and the request's first unit id.  From the plan table
-// in the kernel arguments, or, without one, by the scan.  Every field is
-// uniform; false when there is no such unit or its request does not fit the
-// batch.
+// prefix keys per unit (F32: of no meaning, always the whole prefix) and the
+// request's first unit id.  From the plan table in the kernel arguments, or,
+// without one, by the scan.  Every field is uniform; false when there is no
+// such unit or its request does not fit the batch.
 struct Unit {
   int32_t r, node_base, n, L, chunk_len;
   int64_t ubase;

@@ -142,6 +142,49 @@ static void check_plan(const Batch &b, int hq, int hkv, int D) {
   CHECK(prev_end == p.units && prev_g == t.merge_blocks, "table totals");
 }
 
+// F32 plans: whole prefixes, 32-row tiles where they give every CU a unit, no
+// workspace, and a table that hands every field back.
+static void check_f32_plan(const Batch &b, int hq, int hkv, int D) {
+  const int B = (int)b.plen.size(), G = hq / hkv;
+  AttnShape shape;
+  if (validate_attn_shape(B, b.indptr.data(), b.plen.data(), hq, hkv, D, 16, ADASERVE_F32, -1, shape) != ADASERVE_OK)
+    return;
+  const AttnPlan p = make_plan(B, b.indptr.data(), b.plen.data(), hkv, G, D, ADASERVE_F32);
+  int64_t units[2] = {0, 0};   // of 16 and of 32 rows
+  for (int r = 0; r < B; ++r) {
+    const int rows = (b.indptr[r + 1] - b.indptr[r]) * G;
+    units[0] += (int64_t)hkv * ((rows + 15) / 16);
+    units[1] += (int64_t)hkv * ((rows + 31) / 32);
+  }
+  const bool wide = units[1] >= 256;
+  CHECK(p.rows_per_tile == (wide ? 32 : 16), "%d rows per tile", p.rows_per_tile);
+  CHECK(p.units == units[wide] && p.row_groups == p.units, "units %lld", (long long)p.units);
+  CHECK(p.padded_grid >= p.units && p.padded_grid % (kXcds * kXcdRun) == 0, "grid");
+  CHECK(!p.needs_combine && p.ws_bytes == 0 && p.ws_o_bytes == 0 && p.ws_ml_bytes == 0, "workspace");
+  for (int r = 0; r < B; ++r) {
+    const int n = b.indptr[r + 1] - b.indptr[r];
+    CHECK(prefix_chunks(b.plen[r], p.chunk_len[r]) == 1, "request %d is split", r);
+    // and what the device rebuilds without a table
+    CHECK(prefix_chunks(b.plen[r], chunk_keys(n, G, p.rows_per_tile, p.chunk_target, p.chunk_floor)) == 1, "request %d", r);
+  }
+  PlanTable t;
+  fill_plan_table(t, B, b.indptr.data(), b.plen.data(), hkv, G, p);
+  CHECK(t.count == (B > kPlanMax ? 0 : B) && t.merge_blocks == 0, "table");
+  std::set<int> reqs;
+  int64_t end = 0;
+  for (int i = 0; i < t.count; ++i) {
+    const PlanEntry &e = t.entry[i];
+    const int r = plan_request(e.request_and_chunk);
+    CHECK(r >= 0 && r < B && reqs.insert(r).second, "entry %d request %d", i, r);
+    const int n = b.indptr[r + 1] - b.indptr[r];
+    CHECK(plan_chunk_keys(e.request_and_chunk) == 0, "chunk of %d", r);   // the whole prefix
+    CHECK(plan_nodes(e.n_and_len) == n && plan_prefix_len(e.n_and_len) == b.plen[r] && e.node_base == b.indptr[r],
+          "sizes of %d", r);
+    end += (int64_t)hkv * row_tiles(n, G, p.rows_per_tile);
+    CHECK(e.unit_end == end && e.group_end == 0, "units of %d", r);
+  }
+}
+
 static bool same_plan(const AttnPlan &x, const AttnPlan &y) {
   return x.rows_per_tile == y.rows_per_tile && x.chunk_target == y.chunk_target && x.chunk_floor == y.chunk_floor &&
          x.chunk_len == y.chunk_len && x.units == y.units && x.padded_grid == y.padded_grid &&
@@ -270,6 +313,7 @@ int main() {
     const int B = 1 + (int)(rng() % (it % 5 == 0 ? 300 : 64));
     const Batch b = random_batch(rng, B, it % 3 ? 128 : 8, it % 4 ? 20000 : 200000);
     check_plan(b, h[0], h[1], it % 2 ? 128 : 64);
+    check_f32_plan(b, h[0], h[1], it % 2 ? 128 : 64);
     if (it % 3 == 0) check_choice(b, h[1], h[0] / h[1], it % 2 ? 128 : 64);
   }
   {
@@ -278,6 +322,7 @@ int main() {
     b.plen = {kMaxPrefixLen, kMaxPrefixLen - 31};
     check_plan(b, 32, 2, 128);
     check_choice(b, 2, 16, 128);
+    check_f32_plan(b, 32, 2, 128);
     check_plan(b, 128, 8, 64);
   }
   {
@@ -291,6 +336,7 @@ int main() {
       }
       check_plan(b, 32, 8, 128);
       check_choice(b, 8, 4, 128);
+      check_f32_plan(b, 32, 8, 128);
     }
   }
   check_plan_cache(rng);
