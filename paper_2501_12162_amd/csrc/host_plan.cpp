@@ -65,19 +65,14 @@ int32_t validate_attn_shape(int32_t num_requests, const int32_t *indptr_host, co
   return ADASERVE_OK;
 }
 
-
-
-// Cost model of the bf16 kernel, measured on MI355X.
+// Cost model of the bf16 kernel on MI355X.
 //  * A call costs kCallUs around its steps (launch, start-up loads, output
 //    writes) and kCombineUs when a prefix is split (the merge).
 //  * Up to two units per CU (one round): a CU streams kCuBytesPerUs with one
 //    unit and is credited kPairBytesPerUs more with two (above the measured
 //    2-3e3: more streams also even out slow XCDs); a 32-key step of a unit
 //    alone on its CU takes kStepUs, a step of a second unit beside it kPairUs
-//    and kPairWaveUs for each of its live waves (32 rows).  (Attention of the 16-request 8B batch: 200
-//    units of up to 66 steps 45.5 us, 328 of up to 29 39.0, 512 of up to 15
-//    39.2; a rank of the 70B shape: 294 units 167 us, 512 115-117; long
-//    context: 256 units 209 us, 448 197, 512 195.)
+//    and kPairWaveUs for each of its live waves (32 rows).
 //    Units past the first kFreeStarts hold up each other's first blocks by
 //    kUnitStartUs each.  Short launches run at a higher clock (2.7 GHz against
 //    2.1-2.2 from ~100 us on), which prices the second unit's share down to
@@ -85,6 +80,16 @@ int32_t validate_attn_shape(int32_t num_requests, const int32_t *indptr_host, co
 //  * More units (several rounds): kUnitFixedUs per unit and kBlockUs per step,
 //    dealt longest first, and kChipBytesPerUs.  Head_dim 64 is always priced
 //    this way, streaming by the share of the slots that the units fill.
+// Only kStepUs, kChipBytesPerUs, kCombineUs and the clocks were measured by
+// themselves; kPairBytesPerUs, kFreeStarts, kUnitStartUs, kPairUs, kPairWaveUs
+// and kTileReread are set so that the estimates order such sweeps (estimate |
+// measured, us): attention of the 16-request 8B batch in 200 units 49.1 | 45.5,
+// 328 38.6 | 39.0, 512 35.6 | 39.2; a rank of the 70B shape in 294 212 | 167,
+// 512 129 | 115-117; long context in 256 203 | 209, 448 178 | 197, 512 159 |
+// 195.  They rank the splits of one batch and are not times.  Least so at
+// head_dim 64, where the model has two resident units per CU of 1 us a step
+// and the present kernel (124 VGPRs, 40 KB of LDS) four: 25 requests of 62587
+// keys in 1056 units 767 | 349, in 4092 586 | 334.
 constexpr double kCallUs = 6.0;
 constexpr double kUnitStartUs = 0.02;
 constexpr int kFreeStarts = 167;
