@@ -981,6 +981,14 @@ __global__ __launch_bounds__(kWavesF32 * 64) void tree_attn_f32_kernel(TreeAttnA
   // The values of block b that are not finite, taken out of vr and added to the
   // rows that weigh them.
   auto add_not_finite = [&](const f32x4 (&s)[RB], int b) {
+    bool finite = true;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) finite = finite && fabsf(vr[e][h][i]) < INFINITY;
+    if (__all(finite)) return;
     int64_t stride;
     int rows;
     const float *vb = rows_at(a.v_pages, a.v_tree, b, page, stride, rows);
